@@ -49,8 +49,9 @@ typedef enum {
 #define TAOT_ST_ZERO_MASS 0x4u /* sinkhorn: total supply or demand is zero; T = 0      */
 #define TAOT_ST_UNFILLED 0x8u  /* round_schedule: the auction stopped at t_max with
                                   planned tokens left unassigned (`unfilled` > 0)   */
-#define TAOT_ST_STREAMED 0x10u /* sinkhorn (informational): the plan block did not fit
-                                  on chip and was streamed through device memory    */
+#define TAOT_ST_STREAMED 0x10u /* sinkhorn (informational): the plan block does not fit
+                                  on chip (a path that holds it streams it through
+                                  device memory)                                     */
 
 /* Shape limits (TAOT_ERR_UNSUPPORTED beyond them). */
 #define TAOT_MAX_RANKS 2048
@@ -66,7 +67,8 @@ typedef enum {
 #define TAOT_SK_WAVES_1 0x8u      /* run each register-resident problem on one wave
                                      where its rows fit one wave's registers (by
                                      default small batches spread a problem over
-                                     up to four waves)                              */
+                                     up to four waves, and a tree of cost tiers is
+                                     solved on its groups)                          */
 #define TAOT_SK_DENSE 0x10u       /* dense streamed iterate (Sec. A.2, GEMV form): the
                                      stabilised updates over all R x R entries of
                                      every problem, with no support compaction; each
@@ -179,8 +181,10 @@ size_t taot_plan_loads_noalloc_max_problems(int32_t R, int32_t E);
  * max(sum a_b, 1e-12)); starting from v = 1 on all R columns, `iters`
  * iterations of u = s~ / (M v) then v = d / (M^T u); T = diag(u) M diag(v);
  * then (unless TAOT_SK_NO_COLCAP) T_ij *= min(1, d_j / (sum_i T_ij + 1e-12)).
- * The iterate is computed in fp32 with log-domain stabilisation, so it matches
- * the double-precision definition to rounding (not bit for bit).
+ * The iterate is computed in fp32 with log-domain stabilisation, or, where a
+ * shared cost matrix holds the (at most four) tiers of a tree of groups, in
+ * fp64 on the sums over those groups; either way it matches the
+ * double-precision definition to rounding (not bit for bit).
  *
  *   a, b    [B][R] float   supply and demand (non-negative, finite).
  *   C       [R][R] float   cost; C_batch_stride = 0 shares one matrix, R*R gives

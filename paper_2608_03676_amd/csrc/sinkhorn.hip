@@ -24,7 +24,9 @@
 // The first row update is taken over all R columns (the start v = 1 covers
 // every column).
 //
-// Launches.  sinkhorn_kernel<false> keeps Kt in LDS (one workgroup per problem,
+// Launches.  The tier path (sk_tier.hip) takes the problems of a shared cost
+// matrix that is a tree of topology tiers; the register, LDS and streamed paths
+// below take all others.  sinkhorn_kernel<false> keeps Kt in LDS (one workgroup per problem,
 // all iterations fused); problems whose block does not fit are flagged and
 // handled by sinkhorn_kernel<true>, which streams Kt through device memory
 // (L2-resident at the sizes used here).
@@ -73,15 +75,6 @@ cost_scan_kernel(const float* __restrict__ C, int64_t R2, int32_t chunks, int32_
   if (threadIdx.x == 0) cbad[blockIdx.x] = bad ? 1 : 0;
 }
 
-// Whether problem pb's cost matrix holds a non-finite entry; the chunk marks
-// are read by lane (uniform result over the wave).
-__device__ __forceinline__ bool cost_bad_wave(const SkParams& p, int64_t pb) {
-  const int64_t base = (p.C_stride ? pb : 0) * p.cchunks;
-  bool bad = false;
-  for (int32_t k = threadIdx.x & (kWave - 1); k < p.cchunks; k += kWave) bad |= p.cbad[base + k] != 0;
-  return __ballot(bad) != 0;
-}
-
 // Block-wide exclusive compaction position of `flag` within an NT-thread chunk.
 template <int NT = kSkThreads>
 __device__ __forceinline__ int32_t chunk_compact(bool flag, int32_t* wave_cnt, int32_t& total) {
@@ -118,6 +111,10 @@ __global__ void __launch_bounds__(NT) sinkhorn_kernel(SkParams p) {
   const float* bd = p.b + pb * R;
   const float* Cb = p.C + pb * p.C_stride;
 
+  if (p.cls && p.cls[pb] == kTierClass) {  // already solved (uniform per block)
+    if (!STREAM && tid == 0) p.stream_flag[pb] = 0;
+    return;
+  }
   if (STREAM && !p.all_streamed && p.stream_flag[pb] == 0) return;  // uniform per block
 
   int32_t* hidx = reinterpret_cast<int32_t*>(lds);
@@ -344,8 +341,13 @@ __global__ void __launch_bounds__(kSkThreads) wave_order_kernel(const int32_t* _
                                                                 int32_t* __restrict__ multi,
                                                                 int32_t* __restrict__ single,
                                                                 int32_t* __restrict__ wide,
-                                                                int32_t* __restrict__ counts) {
+                                                                int32_t* __restrict__ counts,
+                                                                const int32_t* __restrict__ left) {
   __shared__ int32_t bins[3][64];  // multi, single, wide (bin 0) counts, then cursors
+  if (left && left[0] == 0) {  // every problem is solved
+    if (threadIdx.x < 3) counts[threadIdx.x] = 0;
+    return;
+  }
   for (int q = threadIdx.x; q < 3 * 64; q += kSkThreads) (&bins[0][0])[q] = 0;
   __syncthreads();
   auto key = [&](int32_t c, int& list) {
@@ -765,20 +767,27 @@ sinkhorn_wide_kernel(SkParams p, const int32_t* __restrict__ list, const int32_t
 // register kernel.  W = 4 when every problem can hold four 128-VGPR waves at
 // once (four SIMDs per compute unit, four such waves per SIMD), else 2
 // (TAOT_SK_WAVES_1 forces W = 2, i.e. one wave per problem where it fits).
-taot_status launch_wave(const SkParams& p, int32_t* cls, int32_t* lists, int32_t* counts, hipStream_t stream) {
+// With a tier workspace the tier path runs first and gives the classes.
+taot_status launch_wave(const SkParams& p, const TierWs* tier, int32_t* cbad, int32_t* cls, int32_t* lists,
+                        int32_t* counts, hipStream_t stream) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     return TAOT_ERR_LAUNCH;
   const int64_t cap = (int64_t)cus * 4 * 4;
   const int W = (4 * (int64_t)p.B <= cap && !(p.flags & TAOT_SK_WAVES_1)) ? 4 : 2;
-  hipLaunchKernelGGL(wave_class_kernel, dim3((unsigned)p.B), dim3(kWave), 0, stream, p, cls);
-  if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
+  if (tier) {
+    const taot_status st = launch_tier(p, *tier, cls, cbad, stream);
+    if (st != TAOT_OK) return st;
+  } else {
+    hipLaunchKernelGGL(wave_class_kernel, dim3((unsigned)p.B), dim3(kWave), 0, stream, p, cls);
+    if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
+  }
   int32_t* multi = lists;
   int32_t* single = lists + p.B;
   int32_t* wide = lists + 2 * (int64_t)p.B;
   hipLaunchKernelGGL(wave_order_kernel, dim3(1), dim3(kSkThreads), 0, stream, cls, p.B, W, multi, single, wide,
-                     counts);
+                     counts, tier ? tier->left : nullptr);
   if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   // two-wave shapes run in eight-wave groups while their LDS slices fit 64 KB
   const bool g8 = 8 * single_lds_bytes(p.R) <= 65536;
@@ -786,6 +795,8 @@ taot_status launch_wave(const SkParams& p, int32_t* cls, int32_t* lists, int32_t
                          : g8   ? launch_reg_w2g8(p, multi, single, counts, stream)
                                 : launch_reg_w2g2(p, multi, single, counts, stream);
   if (st != TAOT_OK) return st;
+  // up to 64 ranks a register class holds every problem
+  if (p.R <= 64) return TAOT_OK;
   // the wide problems: at most one workgroup per compute unit at a time
   const size_t lds = wide_lds_bytes(p.R);
   if (lds > 65536 && hipFuncSetAttribute((const void*)sinkhorn_wide_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -804,11 +815,12 @@ struct SkWs {
   int32_t* cls;     // [B] register class
   int32_t* lists;   // [3][B] register problems: multi, single, wide
   int32_t* counts;  // [3]
-  int32_t* cbad;    // [B or 1][scan_chunks(R)] chunk marks of the cost scan
+  int32_t* cbad;    // [B or 1][scan_chunks(R)] chunk marks of the cost scan (tier path: [R])
   float* kt;
   int64_t kt_stride;
   float* dn;        // [B][dn_stride] state of the dense streamed iterate
   int64_t dn_stride;
+  TierWs tier;
   size_t bytes;
 };
 
@@ -819,11 +831,21 @@ SkWs carve(void* ws, int32_t B, int32_t R) {
   w.cls = c.take<int32_t>((size_t)B);
   w.lists = c.take<int32_t>((size_t)3 * B);
   w.counts = c.take<int32_t>(3);
-  w.cbad = c.take<int32_t>((size_t)B * scan_chunks(R));
+  w.cbad = c.take<int32_t>(std::max((size_t)B * scan_chunks(R), (size_t)R));
   w.kt_stride = round_up((int64_t)R * R, 64);
   w.kt = c.take<float>((size_t)B * w.kt_stride);
   w.dn_stride = round_up((int64_t)dense_state_floats(R), 64);
   w.dn = c.take<float>((size_t)B * w.dn_stride);
+  w.tier.tree = c.take<TierTree>(1);
+  w.tier.left = c.take<int32_t>(1);
+  w.tier.rv = c.take<float4>((size_t)R);
+  w.tier.rcnt = c.take<int4>((size_t)R);
+  w.tier.rlab = c.take<int4>((size_t)R);
+  w.tier.rmore = c.take<int4>((size_t)R);
+  w.tier.k0 = c.take<double>((size_t)R);
+  w.tier.slot = c.take<int32_t>((size_t)R);
+  w.tier.next = c.take<int32_t>((size_t)R);
+  w.tier.head = c.take<int32_t>(256);
   w.bytes = c.off;
   return w;
 }
@@ -838,19 +860,26 @@ taot_status launch_sinkhorn(const float* a, const float* b, int32_t B, int32_t R
   if (B == 0) return TAOT_OK;
   SkWs w = carve(ws, B, R);
   SkParams p{a, b, B, R, C, C_stride, eps, iters, flags, T, f, g, status, w.flag, w.kt, w.kt_stride, 0, 0,
-             w.cbad, scan_chunks(R), w.dn, w.dn_stride};
-  {
+             w.cbad, scan_chunks(R), w.dn, w.dn_stride, nullptr};
+  const bool dense = (flags & (TAOT_SK_DENSE | TAOT_SK_LINEAR)) != 0;
+  const bool wave = !dense && !(flags & (TAOT_SK_FORCE_STREAM | TAOT_SK_NO_REGISTER));
+  // a shared cost matrix may be a tree of tiers (TAOT_SK_WAVES_1 asks for the register path)
+  const bool tier = wave && C_stride == 0 && !(flags & TAOT_SK_WAVES_1);
+  if (tier) {
+    p.cchunks = R;  // the tier prepass marks rows
+  } else {
     const int64_t mats = C_stride ? B : 1;
     hipLaunchKernelGGL(cost_scan_kernel, dim3((unsigned)(mats * p.cchunks)), dim3(kScanThreads), 0, stream, C,
                        (int64_t)R * R, p.cchunks, w.cbad);
     if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   }
-  if (flags & (TAOT_SK_DENSE | TAOT_SK_LINEAR)) return launch_dense(p, stream);
+  if (dense) return launch_dense(p, stream);
   const size_t vec_bytes = (size_t)kVecArrays * R * sizeof(float);
   const bool lds_path = R <= kLdsMaxR;
-  if (!(flags & (TAOT_SK_FORCE_STREAM | TAOT_SK_NO_REGISTER))) {
-    const taot_status st = launch_wave(p, w.cls, w.lists, w.counts, stream);
+  if (wave) {
+    const taot_status st = launch_wave(p, tier ? &w.tier : nullptr, w.cbad, w.cls, w.lists, w.counts, stream);
     if (st != TAOT_OK) return st;
+    p.cls = w.cls;
   }
   if (lds_path) {
     p.lds_kt_cap = (int32_t)max_block(R);

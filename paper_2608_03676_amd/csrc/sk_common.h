@@ -3,6 +3,8 @@
 // paths and the launchers of the register kernels (one unit each).
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace taot {
@@ -30,6 +32,31 @@ struct SkParams {
   int32_t cchunks;       // chunks of kScanChunk entries per cost matrix
   float* dn_ws;          // dense streamed iterate: per-problem state, dn_stride floats each
   int64_t dn_stride;
+  const int32_t* cls;    // [B] class of every problem (nullptr: no class prepass)
+};
+
+// What the tier path finds out about a shared cost matrix, in the workspace.
+struct TierTree {
+  int32_t ok;        // the row scans describe a tree of tiers
+  int32_t mismatch;  // some entry of C disagrees with it
+  int32_t nbits;     // slots = 2^nbits
+  int32_t cut[2];    // address bits below which two slots are in tier 2 (3) at most
+  float c[4];        // costs of the tiers, ascending
+  double m[4];       // exp(-(c_l - c_1) / eps)
+  double w[9];       // weight of the sum after each butterfly step
+  double shift;      // c_1
+};
+struct TierWs {
+  TierTree* tree;
+  int32_t* left;   // [1] 1 = some problem is left to the other kernels
+  float4* rv;      // [R] distinct off-diagonal costs of a row, ascending, then +inf
+  int4* rcnt;      // [R] how often each occurs
+  int4* rlab;      // [R] lowest rank within that cost
+  int4* rmore;     // [R] number of costs, next rank at the smallest, diagonal (bits), non-finite
+  double* k0;      // [R] sum_j exp(-(C_ij - c_1) / eps)
+  int32_t* slot;   // [R]
+  int32_t* next;   // [R] the next rank of the same leaf, or R
+  int32_t* head;   // [256] the first rank of each slot's leaf, or R
 };
 
 namespace {
@@ -43,10 +70,20 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kLdsMaxR = 256;            // beyond this every problem is streamed
 constexpr int kVecArrays = 11;           // per-problem vectors of length R in LDS
+constexpr int32_t kTierClass = -1;       // class of a problem that the tier kernel has solved
 
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float flog2(float x) { return __builtin_amdgcn_logf(x); }
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
+
+// Whether problem pb's cost matrix holds a non-finite entry; the chunk marks
+// are read by lane (uniform result over the wave).
+__device__ __forceinline__ bool cost_bad_wave(const SkParams& p, int64_t pb) {
+  const int64_t base = (p.C_stride ? pb : 0) * p.cchunks;
+  bool bad = false;
+  for (int32_t k = threadIdx.x & (kWave - 1); k < p.cchunks; k += kWave) bad |= p.cbad[base + k] != 0;
+  return __ballot(bad) != 0;
+}
 
 // Register classes: CPL columns per lane (|C| <= 64*CPL) and 8*C8 rows
 // (|H| <= 8*C8).  Class 0 is every other problem (degenerate, larger, or the
@@ -245,6 +282,10 @@ taot_status launch_reg_w2g8(const SkParams& p, const int32_t* multi, const int32
                             hipStream_t stream);
 taot_status launch_reg_w2g2(const SkParams& p, const int32_t* multi, const int32_t* single, const int32_t* counts,
                             hipStream_t stream);
+// The tier path: the prepass over a shared cost matrix (also its validation,
+// one mark per row in cbad), then every problem it can take solved and the
+// class of every other in cls (w.left[0] = 1 if there is one).
+taot_status launch_tier(const SkParams& p, const TierWs& w, int32_t* cls, int32_t* cbad, hipStream_t stream);
 // The dense streamed iterate (TAOT_SK_DENSE) and its per-problem state in the
 // streamed-plan storage of the workspace.
 taot_status launch_dense(const SkParams& p, hipStream_t stream);

@@ -26,7 +26,7 @@
 //       column in a fixed order and sets v_j.
 // All reductions run in a fixed order, so results do not depend on
 // scheduling.
-#include <type_traits>
+
 
 #include "sk_common.h"
 
