@@ -837,12 +837,9 @@ struct LdsState {
   // Phase 3 (aliases the Phase-2 region)
   double* price; uint32_t* rkey; int32_t* work; uint16_t* sstate;
   uint64_t* vmask; uint32_t* vwords; int32_t* dexp; int32_t* dmap; int32_t* cnt; uint64_t* planes;
-  // relative counts: lvl0 [TW] the ranks at the base count, lvl1 [TW] those
-  // one service above it, rel [kRelPlanes] [TW] the code planes, p0 the
-  // price of the base count; misc: base,
-  // minimum (rebase scratch), a base-count word emptied (2, by round parity),
-  // a transfer made (2, by round parity), the base's epoch (rebases so far)
-  uint64_t* lvl0; uint64_t* lvl1; uint64_t* rel; double* p0; int32_t* misc;
+  // relative counts: lvl [2][TW] the ranks at the base count and those one
+  // service above it, rel [kRelPlanes] [TW] the code planes
+  uint64_t* lvl; uint64_t* rel;
   int8_t* cn; double* cv; int32_t* cvr; uint32_t* cw; uint64_t* cm;
   size_t bytes;
 };
@@ -871,17 +868,16 @@ __host__ __device__ inline LdsState<CF> carve_lds(char* base, int32_t R, int32_t
   off = split;
   w.price = (double*)take(8 * R_); w.rkey = (uint32_t*)take(4 * R_);
   w.work = (int32_t*)take(4 * S1);
-  // bid states of the packed layout's list entries, by list position
-  // (several waves, at most two slots per thread; the 4-wave build for few
-  // problems per compute unit leaves them unused)
-  w.sstate = (uint16_t*)take(CF::kT > kWave && S1 <= 2 * (size_t)CF::kT ? 2 * S1 : 0);
+  // the list entries' bid states, by list position, over the candidates' slot
+  // expert indices (read last when the list's items are built)
+  w.dmap = (int32_t*)take(2 * S1 > 4 * N_ ? 2 * S1 : 4 * N_);
+  w.sstate = (uint16_t*)w.dmap;
   // the word lists guide the per-word search of sets wider than 4 words only
   w.vmask = (uint64_t*)take(8 * DC * TW); w.vwords = (uint32_t*)take(TW > 4 ? 4 * DC : 0);
-  w.dexp = (int32_t*)take(4 * DC); w.dmap = (int32_t*)take(4 * N_);
+  w.dexp = (int32_t*)take(4 * DC);
   w.cnt = (int32_t*)take(4 * R_); w.planes = (uint64_t*)take(8 * CF::kPL * TW);
-  w.lvl0 = (uint64_t*)take(8 * TW); w.lvl1 = (uint64_t*)take(8 * TW);
+  w.lvl = (uint64_t*)take(2 * 8 * TW);
   w.rel = (uint64_t*)take(8 * kRelPlanes * TW);
-  w.p0 = (double*)take(8); w.misc = (int32_t*)take(4 * 8);
   w.cn = (int8_t*)take(SC);
   w.cv = (double*)take(8 * SC * kTierMax); w.cvr = (int32_t*)take(4 * SC * kTierMax);
   w.cw = (uint32_t*)take(4 * SC * kTierMax);
@@ -902,7 +898,6 @@ struct LdsParams {
   int32_t* fallback;     // [B] 1 = left to schedule_kernel
   int32_t* nprime;       // [B][DC][R]
   int32_t NEC;           // candidate-expert capacity of the LDS layout
-  int32_t shared;        // 1 when the batch has more problems than compute units
 };
 
 // Block-wide OR with one barrier; flags alternate between two halves of buf
@@ -953,17 +948,452 @@ __device__ __forceinline__ int32_t wave_max_i32(int32_t v) {
   return max((int32_t)r32[0], (int32_t)r32[1]);
 }
 
-// One problem per workgroup of CF::kT threads; thread i bids for list entries
-// i, i + kT, ... (SPL of them).  WPE waves per SIMD bound the registers: a
-// batch that fills the chip needs all its problems resident at once, a
-// smaller one is better served without the register cap.
-template <class CF, int SPL, int WPE>
+// The rounds of the auction, on one wave of the problem's workgroup; returns
+// how many ran.
+//
+// Every bid names a rank, which then serves its best bidder with a positive
+// amount; so every group with an open slot and a valid rank bids again in
+// every round.  A group drops out once its slots are full or it finds no valid
+// rank (validity only ends).  A round is
+//   X: each listed group bids and posts a key to the rank it bid for;
+//   Y: a group whose key stands moves tokens; the others lose.
+// A round without a bid ends the auction.
+//
+// What bounds it: the rounds follow from one another (about 1200 at R = 256,
+// 10000 at R = 1024) and hold few transfers (4 to 6) for the list they walk,
+// so a round costs its chain of latencies.  One wave runs it without a barrier,
+// as the LDS operations of a wave stay in order; lists of up to 64 groups stay
+// in registers, a group to a lane, longer ones are walked 64 at a time.
+//
+// Incremental bids.  Within an epoch (while the base count stays) a group keeps
+// its first tier ts that holds a valid rank, the fewest services lev (above the
+// base count) among that tier's valid ranks, and the lowest 64-rank word w of
+// the tier with a valid rank that has them.  Its bid is the lowest such rank of
+// the word.  All three only move forward: validity only ends and counts only
+// rise, so a rank can reach lev services only from fewer, which no valid rank of
+// the tier has.  A rank that drains for the group's expert was served and left
+// the level with that, so the word's valid ranks (win) need not be read again
+// while the level lasts.  When the word runs out the search goes on from it, and
+// when the level does, it looks for the tier's smallest relative code.  Prices
+// are functions of the count, so whether a later tier can reach the bid's score
+// is settled for as long as the level lasts; only a group for which none can
+// keeps its state (has).  Empty tiers stay empty: ts holds across epochs.
+//
+// Transfers.  A slot that plans more than any rank holds of its expert (nmax)
+// takes all that the rank has, so its round does not wait for the count to
+// arrive from device memory: the lane keeps the load in flight and books it
+// with its next transfer.
+//
+// List entries: slot, slot-expert index, host structure (0-25); negative: none.
+// Entry states: w (0-3), ts (4-5), lev (6-9), has (10), epoch parity (11: a
+// listed group's state is rewritten in every round that does not bid from it,
+// and the base moves at most once per round).  Between the two steps of a round
+// over a longer list the spare bits hold the bit of the bid's rank in word w:
+// two bits in the entry (26-27), four in the state (12-15).
+template <class CF>
+__device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const int16_t* gnext, int32_t* np,
+                                                  int32_t* Xb, int32_t R, int32_t S, int32_t nw, double step,
+                                                  int64_t tmax) {
+  constexpr int TW = CF::kTW;
+  constexpr int32_t kSlotMask = (1 << kItemSlotBits) - 1, kExpMask = (1 << kItemExpertBits) - 1;
+  constexpr int32_t kItemBits = 26, kItemMask = (1 << kItemBits) - 1;
+  constexpr int32_t kStructMask = (1 << (kItemBits - kItemSlotBits - kItemExpertBits)) - 1;
+  constexpr uint32_t kHas = 1u << 10, kStateMask = (1u << 12) - 1u;
+  static_assert(TW <= 16 && kTierMax <= 4 && kRelMax <= 15 && CF::kSC <= kStructMask + 1, "entry and state fields");
+  const int lane = threadIdx.x & (kWave - 1);
+  const bool track = step > 0.0;  // counts order the prices; with step 0 all prices stay 0
+  uint32_t* rk = L.rkey;
+  const int32_t* nmax = L.dexp;
+  double P0 = 0.0;                // price of the base count
+  int32_t base = 0, base_left = R;
+  uint32_t epoch = 0;             // parity
+  bool planes_on = false;         // the planes of the full counts are kept from their first use on
+
+  auto expert = [](int32_t it) { return (it >> kItemSlotBits) & kExpMask; };
+  auto structure = [](int32_t it) { return (it >> (kItemSlotBits + kItemExpertBits)) & kStructMask; };
+  // ranks of word w with exactly lev services above the base count
+  auto level = [&](uint32_t lev, int w) {
+    if (lev < 2u) return L.lvl[lev * TW + w];
+    uint64_t m = ~0ull;
+#pragma unroll
+    for (int j = 0; j < kRelPlanes; ++j) m &= ((lev >> j) & 1u) ? L.rel[j * TW + w] : ~L.rel[j * TW + w];
+    return m;
+  };
+  struct Bid {
+    int32_t r, v;    // rank (-1: no valid rank is left), bonus rank
+    uint32_t state;
+    uint64_t win;    // valid ranks of the state's word
+  };
+  // The search from the entry's state on; stuck: every candidate's code is
+  // saturated and the count planes are off.
+  auto search = [&](int32_t it, uint32_t state, bool& stuck) {
+    const int32_t d = expert(it), st = structure(it);
+    const uint64_t* vm = L.vmask + d * TW;
+    const int32_t nt = L.cn[st];
+    const uint32_t vw = TW > 4 ? L.vwords[d] : ~0u;
+    const int32_t ts = (int32_t)(state >> 4) & 3;
+    const bool same = (state & kHas) != 0u && (state >> 11) == epoch;
+    double bs = -INFINITY;
+    Bid b{-1, 0, state & (3u << 4), 0ull};
+    int found = 0;  // tiers with a valid rank that were looked at
+    for (int32_t ti = ts; ti < nt; ++ti) {
+      const double v = L.cv[st * kTierMax + ti];
+      if (found && v - P0 < bs) break;  // no score in this tier or the next reaches bs
+      const uint64_t* tm = L.cm + (st * kTierMax + ti) * TW;
+      const uint32_t words = L.cw[st * kTierMax + ti] & vw;
+      const bool resume = same && ti == ts;
+      const uint32_t lev = resume ? (state >> 6) & 15u : 0u;
+      int32_t rr = -1;
+      uint32_t code = lev;
+      uint64_t win = 0ull;
+      // the lowest valid rank at the base count or one service above it
+      if (lev < 2u)
+        for (uint32_t ws = resume ? words & (~0u << (state & 15u)) : words; ws; ws &= ws - 1u) {
+          const int w = __builtin_ctz(ws);
+          const uint64_t c = tm[w] & vm[w], h = c & L.lvl[lev * TW + w];
+          if (h) {
+            rr = w * kWave + __builtin_ctzll(h);
+            win = c;
+            break;
+          }
+        }
+      if (rr < 0) {
+        // the smallest relative code (words ascend: equal codes keep the lower rank)
+        uint32_t best = kRelMax + 1;
+        for (uint32_t ws = words; ws; ws &= ws - 1u) {
+          const int w = __builtin_ctz(ws);
+          const uint64_t all = tm[w] & vm[w];
+          uint64_t c = all, p[kRelPlanes];
+#pragma unroll
+          for (int j = 0; j < kRelPlanes; ++j) p[j] = L.rel[j * TW + w];
+          if (!c) continue;
+          uint32_t cw = 0;
+#pragma unroll
+          for (int j = kRelPlanes - 1; j >= 0; --j) {
+            const uint64_t m = c & ~p[j];
+            if (m) c = m;
+            else cw |= 1u << j;
+          }
+          if (cw < best) {
+            best = cw;
+            rr = w * kWave + __builtin_ctzll(c);
+            win = all;
+          }
+        }
+        if (rr < 0) continue;  // no valid rank in this tier
+        code = best;
+        if (code == (uint32_t)kRelMax && track) {
+          stuck |= !planes_on;
+          // all saturated: the smallest full count
+          uint32_t cmin = 0xFFFFFFFFu;
+          for (uint32_t ws = planes_on ? words : 0u; ws; ws &= ws - 1u) {
+            const int w = __builtin_ctz(ws);
+            uint64_t x = tm[w] & vm[w];
+            if (!x) continue;
+            uint32_t mn = 0;
+            for (int32_t j = CF::kPL - 1; j >= 0; --j) {
+              const uint64_t m = x & ~L.planes[j * TW + w];
+              if (m) x = m;
+              else mn |= 1u << j;
+            }
+            if (mn < cmin) {
+              cmin = mn;
+              rr = w * kWave + __builtin_ctzll(x);
+            }
+          }
+        }
+      }
+      if (found == 0) {
+        b.state = (uint32_t)(rr >> 6) | ((uint32_t)ti << 4) | (code << 6) | (epoch << 11) |
+                  (track && code < (uint32_t)kRelMax ? kHas : 0u);
+        b.win = win;
+      }
+      ++found;
+      const double sc = v - (code == 0u ? P0 : L.price[rr]);
+      if (sc > bs || (sc == bs && rr < b.r)) {
+        bs = sc;
+        b.r = rr;
+        b.v = L.cvr[st * kTierMax + ti];
+      }
+    }
+    if (found > 1) {  // the tiers compete: search again in the next round
+      b.state = (b.state & (3u << 4)) | (uint32_t)(b.r >> 6);
+    }
+    return b;
+  };
+  // (wave-uniform) the search of the flagged lanes; the count planes come into
+  // being when a lane first needs them
+  auto search_all = [&](bool need, int32_t it, Bid& b) {
+    bool stuck = false;
+    Bid x = b;
+    if (need) x = search(it, b.state, stuck);
+    if (__ballot(stuck) != 0) {
+      for (int w = 0; w < TW; ++w) {
+        const int32_t r = w * kWave + lane;
+        const int32_t c = r < R ? L.cnt[r] : 0;
+        for (int j = 0; j < CF::kPL; ++j) {
+          const uint64_t m = __ballot((c >> j) & 1);
+          if (lane == 0) L.planes[j * TW + w] = m;
+        }
+      }
+      planes_on = true;
+      if (need) x = search(it, b.state, stuck);
+    }
+    b = x;
+  };
+  // The bookkeeping of a service of rank r, which had c0 services at price pr;
+  // returns whether it leaves the base count.
+  auto serve = [&](int32_t r, int32_t c0, double pr) {
+    rk[r] = 0u;  // the rank's key is cleared for the next round
+    L.price[r] = pr + step;
+    if (!track) return false;
+    const unsigned long long bit = 1ull << (r & 63);
+    const int w = r >> 6;
+    const int32_t c1 = c0 + 1, k0 = c0 - base;
+    L.cnt[r] = c1;
+    if (planes_on)
+      for (uint32_t flip = (uint32_t)(c0 ^ c1); flip; flip &= flip - 1)
+        atomicXor(reinterpret_cast<unsigned long long*>(&L.planes[__builtin_ctz(flip) * TW + w]), bit);
+    // the relative code rises by one (below saturation)
+    if (k0 < kRelMax)
+      for (uint32_t flip = (uint32_t)(k0 ^ (k0 + 1)); flip; flip &= flip - 1)
+        atomicXor(reinterpret_cast<unsigned long long*>(&L.rel[__builtin_ctz(flip) * TW + w]), bit);
+    // the rank leaves the base count, enters (code 0 -> 1) or leaves (1 -> 2) the set one above it
+    if (k0 == 0) atomicXor(reinterpret_cast<unsigned long long*>(&L.lvl[w]), bit);
+    if (k0 <= 1) atomicXor(reinterpret_cast<unsigned long long*>(&L.lvl[TW + w]), bit);
+    return k0 == 0;
+  };
+  // rank r holds no more tokens of slot expert d
+  auto drained = [&](int32_t d, int32_t r) {
+    const unsigned long long bit = 1ull << (r & 63);
+    const int w = r >> 6;
+    const uint64_t old = atomicAnd(reinterpret_cast<unsigned long long*>(&L.vmask[d * TW + w]), ~bit);
+    if constexpr (TW > 4)  // the word list only guides the search
+      if ((old & ~bit) == 0ull) atomicAnd(&L.vwords[d], ~(1u << w));
+  };
+  // Every rank has left the base count: the base moves to the new fewest
+  // services and the relative codes are rebuilt from the counts.
+  auto rebase = [&]() {
+    int32_t mn = INT_MAX;
+    for (int32_t r = lane; r < R; r += kWave) mn = min(mn, L.cnt[r]);
+    base = __builtin_amdgcn_readfirstlane(-wave_max_i32(-mn));
+    base_left = 0;
+    for (int w = 0; w < TW; ++w) {
+      const int32_t r = w * kWave + lane;
+      const int32_t kr = r < R ? min(L.cnt[r] - base, kRelMax) : -1;
+      const uint64_t m0 = __ballot(kr == 0), m1 = __ballot(kr == 1);
+      if (lane == 0) {
+        L.lvl[w] = m0;
+        L.lvl[TW + w] = m1;
+      }
+#pragma unroll
+      for (int j = 0; j < kRelPlanes; ++j) {
+        const uint64_t m = __ballot(kr > 0 && ((kr >> j) & 1));
+        if (lane == 0) L.rel[j * TW + w] = m;
+      }
+      // every rank at the new base has the same price
+      if (m0 != 0ull) P0 = L.price[w * kWave + (int)__builtin_ctzll(m0)];
+      base_left += (int32_t)__popcll(m0);
+    }
+    epoch ^= 1u;
+  };
+
+  int64_t t = 1;
+  // ---- lists longer than a wave: entries and states in LDS -----------------------------
+  int32_t active = nw;
+  for (; t <= tmax && nw > kWave; ++t) {
+    // X: bids
+    int32_t nit = lane < nw ? L.work[lane] : -1;
+    uint32_t nst = lane < nw ? L.sstate[lane] : 0u;
+    int32_t bids = 0;
+    for (int32_t q0 = 0; q0 < nw; q0 += kWave) {
+      const int32_t q = q0 + lane, it = nit & (nit < 0 ? -1 : kItemMask);
+      Bid b{-1, 0, nst & kStateMask, 0ull};
+      if (q0 + kWave < nw) {  // the next entries, while these are looked at
+        const bool in = q + kWave < nw;
+        nit = in ? L.work[q + kWave] : -1;
+        nst = in ? L.sstate[q + kWave] : 0u;
+      }
+      if (it >= 0 && (b.state & kHas) != 0u && (b.state >> 11) == epoch) {
+        const int32_t d = expert(it);
+        const int w = (int)(b.state & 15u), e = structure(it) * kTierMax + (int)((b.state >> 4) & 3u);
+        const uint64_t h = L.cm[e * TW + w] & L.vmask[d * TW + w] & level((b.state >> 6) & 15u, w);
+        b.v = L.cvr[e];
+        if (h) b.r = w * kWave + __builtin_ctzll(h);
+      }
+      const bool need = it >= 0 && b.r < 0;
+      if (__ballot(need) != 0) search_all(need, it, b);
+      if (it >= 0) {
+        if (b.r >= 0) {
+          atomicMax(&rk[b.r], ((uint32_t)b.v << 16) | (uint32_t)(0xFFFF - (it & kSlotMask)));
+          L.sstate[q] = (uint16_t)(b.state | (uint32_t)((b.r & 63) >> 2) << 12);
+          L.work[q] = it | (b.r & 3) << kItemBits;
+        } else {
+          L.work[q] = -1;  // no valid rank is left
+        }
+      }
+      bids += (int32_t)__popcll(__ballot(b.r >= 0));
+    }
+    if (bids == 0) return t - 1;  // no bid: the state is final
+    active = bids;
+    // Y: the winners of all entries, gathered a lane each, then their transfers
+    int32_t wq = -1, have_n = 0;
+    auto transfers = [&]() {
+      bool left_base = false;
+      if (wq >= 0) {
+        int32_t it = L.work[wq];
+        const uint32_t state = L.sstate[wq];
+        const int32_t r = (int32_t)(state & 15u) * kWave + (int32_t)(state >> 12) * 4 + ((it >> kItemBits) & 3);
+        it &= kItemMask;
+        const int32_t s = it & kSlotMask, d = expert(it);
+        const int32_t have = np[(int64_t)d * R + r];
+        const int32_t a = L.amt[s], c0 = L.cnt[r], gn = gnext[s];
+        left_base = serve(r, c0, L.price[r]);
+        const int32_t x = have < a ? have : a;
+        Xb[(int64_t)r * S + s] = x;
+        L.amt[s] = a - x;
+        if (x == have) drained(d, r);
+        else np[(int64_t)d * R + r] = have - x;
+        if (x == a) L.work[wq] = gn >= 0 ? (it & ~kSlotMask) | gn : -1;
+        wq = x == a && gn < 0 ? -2 : -1;  // -2: the group is done
+      }
+      base_left -= (int32_t)__popcll(__ballot(left_base));
+      active -= (int32_t)__popcll(__ballot(wq == -2));
+      wq = -1;
+      have_n = 0;
+    };
+    for (int32_t q0 = 0; q0 < nw; q0 += kWave) {
+      const int32_t q = q0 + lane;
+      const int32_t it = q < nw ? L.work[q] : -1;
+      const uint32_t state = q < nw ? L.sstate[q] : 0u;
+      const int32_t r = (int32_t)(state & 15u) * kWave + (int32_t)(state >> 12) * 4 + ((it >> kItemBits) & 3);
+      // the slot is part of the key, so its low half tells the winner (0: served already)
+      const uint32_t k = it >= 0 ? rk[r] : 0u;
+      const bool won = k != 0u && (k & 0xFFFFu) == (uint32_t)(0xFFFF - (it & kSlotMask));
+      const uint64_t m = __ballot(won);
+      const int32_t c = (int32_t)__popcll(m);
+      if (c == 0) continue;
+      if (have_n + c > kWave) transfers();
+      // lane have_n + j takes the j-th winner of these entries
+      const int32_t j = lane - have_n;
+      if (j >= 0 && j < c) {
+        uint64_t rest = m;
+        for (int32_t u = 0; u < j; ++u) rest &= rest - 1ull;
+        wq = q0 + (int32_t)__builtin_ctzll(rest);
+      }
+      have_n += c;
+    }
+    if (have_n > 0) transfers();
+    if (track && base_left == 0) rebase();
+    if (active <= nw - kWave || active <= kWave) {
+      // a group of lanes less will do: the list closes up in place (an entry
+      // moves to its own place or a lower one)
+      int32_t kept = 0;
+      for (int32_t q0 = 0; q0 < nw; q0 += kWave) {
+        const int32_t q = q0 + lane;
+        const int32_t it = q < nw ? L.work[q] : -1;
+        const uint32_t state = q < nw ? L.sstate[q] : 0u;
+        const uint64_t m = __ballot(it >= 0);
+        const int32_t to = kept + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (it >= 0) {
+          L.work[to] = it;
+          L.sstate[to] = (uint16_t)state;
+        }
+        kept += (int32_t)__popcll(m);
+      }
+      nw = kept;
+    }
+  }
+  // ---- a group per lane, in registers ----------------------------------------------------
+  int32_t it = lane < nw ? L.work[lane] : -1;
+  Bid b{-1, 0, 0u, 0ull};
+  int32_t a = 0, most = 0;   // tokens planned; the most a rank can hold
+  int32_t pr = -1, pv = 0;   // a transfer in flight: its rank and what the rank held
+  if (it >= 0) {
+    it &= kItemMask;
+    b.state = L.sstate[lane] & kStateMask & ~kHas;  // (win is not known)
+    a = L.amt[it & kSlotMask];
+    most = nmax[expert(it)];
+  }
+  auto book = [&]() {  // the transfer in flight
+    Xb[(int64_t)pr * S + (it & kSlotMask)] = pv;
+    a -= pv;
+    pr = -1;
+  };
+  for (; t <= tmax; ++t) {
+    int32_t r = -1;
+    if (it >= 0 && (b.state & kHas) != 0u && (b.state >> 11) == epoch) {
+      const int w = (int)(b.state & 15u);
+      const uint64_t h = b.win & level((b.state >> 6) & 15u, w);
+      if (h) r = w * kWave + __builtin_ctzll(h);
+    }
+    const bool need = it >= 0 && r < 0;
+    if (__ballot(need) != 0) {
+      search_all(need, it, b);
+      if (need) {
+        r = b.r;
+        if (r < 0) {  // no valid rank is left
+          if (pr >= 0) book();
+          L.amt[it & kSlotMask] = a;
+          it = -1;
+        }
+      }
+    }
+    if (__ballot(it >= 0) == 0) break;  // no bid: the state is final
+    const uint32_t key = ((uint32_t)b.v << 16) | (uint32_t)(0xFFFF - (it & kSlotMask));
+    bool won = false, left_base = false;
+    if (it >= 0) {
+      atomicMax(&rk[r], key);
+      // (the rank's count and price come with the key)
+      const uint32_t k = *(volatile uint32_t*)&rk[r];
+      const int32_t c0 = *(volatile int32_t*)&L.cnt[r];
+      const double price = *(volatile double*)&L.price[r];
+      won = k == key;
+      if (won) {
+        if (pr >= 0) book();
+        pv = np[(int64_t)expert(it) * R + r];
+        pr = r;
+        left_base = serve(r, c0, price);
+      }
+    }
+    base_left -= (int32_t)__popcll(__ballot(left_base));
+    const bool wait = won && a <= most;  // the slot may fill
+    if (won && !wait) drained(expert(it), r);
+    if (__ballot(wait) != 0) {
+      if (wait) {
+        const int32_t d = expert(it), s = it & kSlotMask, have = pv;
+        if (have <= a) drained(d, r);
+        else np[(int64_t)d * R + r] = have - a;
+        pv = have < a ? have : a;
+        book();
+        if (a == 0) {
+          const int32_t gn = gnext[s];
+          L.amt[s] = 0;
+          it = gn >= 0 ? (it & ~kSlotMask) | gn : -1;
+          if (gn >= 0) a = L.amt[gn];
+        }
+      }
+    }
+    if (track && base_left == 0) rebase();
+  }
+  if (it >= 0) {
+    if (pr >= 0) book();
+    L.amt[it & kSlotMask] = a;
+  }
+  return t - 1;
+}
+
+// One problem per workgroup of CF::kT threads; the auction's rounds run on one
+// of its waves.  WPE waves per SIMD bound the registers: a batch that fills
+// the chip needs all its problems resident at once, a smaller one is better
+// served without the register cap.
+template <class CF, int WPE>
 __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp) {
   constexpr int NT = CF::kT, NW = NT / kWave, TW = CF::kTW;
   extern __shared__ __attribute__((aligned(16))) char lds_dyn[];
   __shared__ int32_t wave_cnt[NW];
   __shared__ int32_t flagbuf[2 * NW];
-  __shared__ int32_t sh_maxc, sh_nw[2];
+  __shared__ int32_t sh_nw, simd_of[NW];
   __shared__ unsigned long long sh_sum, sh_big;
   const SchParams& p = wp.s;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
@@ -993,7 +1423,7 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
     const int32_t h = p.home[e];
     badh |= h < 0 || h >= R;
   }
-  if (tid == 0) { sh_sum = 0; sh_big = 0; sh_maxc = 0; }
+  if (tid == 0) { sh_sum = 0; sh_big = 0; sh_nw = 0; }
   if (block_or<NT>(badh, flagbuf, parity)) {
     for (int32_t s = tid; s < S; s += NT) { se[s] = -1; sa[s] = 0; }
     for (int64_t q = tid; q < (int64_t)R * S; q += NT) Xb[q] = 0;
@@ -1184,6 +1614,7 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
   const int32_t* nb = p.n + b * (int64_t)R * E;
   if constexpr (TW > 4)
     for (int32_t d = tid; d < D; d += NT) L.vwords[d] = 0u;
+  for (int32_t d = tid; d < D; d += NT) L.work[d] = 0;  // D <= S
   __syncthreads();
   // (wave w takes word w, rank r on its lane; the strided loads of eight
   // experts are issued before any is used)
@@ -1200,7 +1631,9 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
         if (d >= D) break;
         if (r < R) np[(int64_t)d * R + r] = v[u];
         const uint64_t m = __ballot(v[u] > 0);
+        const int32_t most = wave_max_i32(v[u]);
         if (lane == 0) {
+          atomicMax(&L.work[d], most);
           L.vmask[d * TW + wid] = m;
           if constexpr (TW > 4)
             if (m) atomicOr(&L.vwords[d], 1u << wid);
@@ -1208,90 +1641,79 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
       }
     }
   }
-  // the active-slot list of the first round: every slot with tokens planned
-  // (packed layout: the first slot of each bid group, see below)
-  // (the packed list pays where the bid search competes for issue slots: the
-  // 16-wave layout, and the 4-wave one when it runs many problems per
-  // compute unit; with few problems per compute unit a round is a chain of
-  // latencies, and compacting the list only lengthens it)
-  constexpr bool kPack = SPL <= 2 && (TW > 4 || (NW > 1 && WPE > 1));
-  if (tid < 2) sh_nw[tid] = 0;
+  // from here on dexp holds the most tokens of each slot expert on any rank
+  __syncthreads();
+  for (int32_t d = tid; d < D; d += NT) L.dexp[d] = L.work[d];
+  __syncthreads();
+  // The list of the first round: the first slot of each bid group.
+  // Bid groups.  Two open slots with the same host tier structure and the
+  // same expert (the item's bits above the slot) make the same bid: the
+  // search reads only those and the shared state.  Their keys then differ
+  // in the slot alone, so the lower slot wins wherever both bid, and a
+  // slot of a group can only be served once every lower open slot of the
+  // group is full.  A group without a valid rank is without one for all
+  // its slots (validity depends on the expert only).  So each group bids
+  // with its lowest open slot only; when that slot fills, the next open
+  // slot of the group takes its place (and its bid state, which depends on
+  // the group alone).  The rounds, bids and transfers are the same as
+  // with every open slot bidding.  The items are built once, by slot, in
+  // the list array (-1: no tokens planned).
   auto slot_item = [&](int32_t s, bool& f) {
     const int32_t ec = s < S ? L.slot_ec[s] : -1;
     f = ec >= 0 && L.amt[s] > 0;
     return f ? s | (L.dmap[ec] << kItemSlotBits) | (wp.sidx[s / K] << (kItemSlotBits + kItemExpertBits)) : 0;
   };
-  // packed layout: the next open slot of each slot's bid group (-1: none),
-  // over the slot experts, which nothing reads once the items are built
+  // the next open slot of each slot's bid group (-1: none), over the slot
+  // experts, which nothing reads once the items are built
   int16_t* const gnext = L.slot_ec;
-  if constexpr (kPack) {
-    // Bid groups.  Two open slots with the same host tier structure and the
-    // same expert (the item's bits above the slot) make the same bid: the
-    // search reads only those and the shared state.  Their keys then differ
-    // in the slot alone, so the lower slot wins wherever both bid, and a
-    // slot of a group can only be served once every lower open slot of the
-    // group is full.  A group without a valid rank is without one for all
-    // its slots (validity depends on the expert only).  So each group bids
-    // with its lowest open slot only; when that slot fills, the next open
-    // slot of the group takes its place (and its bid state, which depends on
-    // the group alone).  The rounds, bids and transfers are the same as
-    // with every open slot bidding.  The items are built once, by slot, in
-    // the list array (-1: no tokens planned).
-    for (int32_t s = tid; s < S; s += NT) {
-      bool f;
-      const int32_t item = slot_item(s, f);
-      L.work[s] = f ? item : -1;
-    }
-    __syncthreads();
-    for (int32_t s = tid; s < S; s += NT) {
-      const int32_t it0 = L.work[s];
-      int32_t nx = -1;
-      if (it0 >= 0) {
-        // the group key; a slot without tokens (-1) has key -1
-        const int32_t k = it0 >> kItemSlotBits;
-        int32_t q = s + 1;
-        for (; q < S && (q & 3); ++q)
-          if ((L.work[q] >> kItemSlotBits) == k) { nx = q; break; }
-        if (nx < 0) {
-          // four items per 16-byte load (the list array is 16-byte aligned)
-          for (; q + 3 < S; q += 4) {
-            const int4 w4 = *reinterpret_cast<const int4*>(L.work + q);
-            const bool x0 = (w4.x >> kItemSlotBits) == k, x1 = (w4.y >> kItemSlotBits) == k,
-                       x2 = (w4.z >> kItemSlotBits) == k, x3 = (w4.w >> kItemSlotBits) == k;
-            if (x0 || x1 || x2 || x3) {
-              nx = x0 ? q : x1 ? q + 1 : x2 ? q + 2 : q + 3;
-              break;
-            }
-          }
-          if (nx < 0)
-            for (; q < S; ++q)
-              if ((L.work[q] >> kItemSlotBits) == k) { nx = q; break; }
-        }
-      }
-      gnext[s] = (int16_t)nx;
-    }
-    __syncthreads();
-    // a slot with a lower open slot in its group waits: its item is marked
-    // negative (one writer per slot)
-    for (int32_t s = tid; s < S; s += NT)
-      if (gnext[s] >= 0) L.work[gnext[s]] |= (int32_t)0x80000000u;
-    __syncthreads();
-    // the groups' first slots, compacted into the list of round 1 (odd)
-    int32_t mine[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) mine[i] = i * NT + tid < S ? L.work[i * NT + tid] : -1;
-    __syncthreads();  // every item is read before the list overwrites the array
-#pragma unroll
-    for (int i = 0; i < 2; ++i) list_append(mine[i] >= 0, mine[i], L.work, &sh_nw[1]);
-  } else {
-    __syncthreads();
-    for (int32_t base = 0; base < S; base += NT) {
-      const int32_t s = base + tid;
-      bool f;
-      const int32_t item = slot_item(s, f);
-      list_append(f, item, L.work, &sh_nw[1]);  // the list of round 1 (odd)
-    }
+  for (int32_t s = tid; s < S; s += NT) {
+    bool f;
+    const int32_t item = slot_item(s, f);
+    L.work[s] = f ? item : -1;
   }
+  __syncthreads();
+  for (int32_t s = tid; s < S; s += NT) {
+    const int32_t it0 = L.work[s];
+    int32_t nx = -1;
+    if (it0 >= 0) {
+      // the group key; a slot without tokens (-1) has key -1
+      const int32_t k = it0 >> kItemSlotBits;
+      int32_t q = s + 1;
+      for (; q < S && (q & 3); ++q)
+        if ((L.work[q] >> kItemSlotBits) == k) { nx = q; break; }
+      if (nx < 0) {
+        // four items per 16-byte load (the list array is 16-byte aligned)
+        for (; q + 3 < S; q += 4) {
+          const int4 w4 = *reinterpret_cast<const int4*>(L.work + q);
+          const bool x0 = (w4.x >> kItemSlotBits) == k, x1 = (w4.y >> kItemSlotBits) == k,
+                     x2 = (w4.z >> kItemSlotBits) == k, x3 = (w4.w >> kItemSlotBits) == k;
+          if (x0 || x1 || x2 || x3) {
+            nx = x0 ? q : x1 ? q + 1 : x2 ? q + 2 : q + 3;
+            break;
+          }
+        }
+        if (nx < 0)
+          for (; q < S; ++q)
+            if ((L.work[q] >> kItemSlotBits) == k) { nx = q; break; }
+      }
+    }
+    gnext[s] = (int16_t)nx;
+  }
+  __syncthreads();
+  // a slot with a lower open slot in its group waits: its item is marked
+  // negative (one writer per slot)
+  for (int32_t s = tid; s < S; s += NT)
+    if (gnext[s] >= 0) L.work[gnext[s]] |= (int32_t)0x80000000u;
+  __syncthreads();
+  // the groups' first slots, compacted
+  constexpr int kSlotsPerThread = CF::kMaxS / NT;
+  int32_t mine[kSlotsPerThread];
+#pragma unroll
+  for (int i = 0; i < kSlotsPerThread; ++i) mine[i] = i * NT + tid < S ? L.work[i * NT + tid] : -1;
+  __syncthreads();  // every item is read before the list overwrites the array
+#pragma unroll
+  for (int i = 0; i < kSlotsPerThread; ++i) list_append(mine[i] >= 0, mine[i], L.work, &sh_nw);
+  for (int32_t s = tid; s < S; s += NT) L.sstate[s] = 0;  // no bid yet
   for (int32_t r = tid; r < R; r += NT) {
     L.price[r] = 0.0;
     L.rkey[r] = 0;
@@ -1301,12 +1723,10 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
   // every rank starts with 0 services: at the base count 0, code 0
   for (int32_t q = tid; q < TW; q += NT) {
     const int32_t lo = q * kWave;
-    L.lvl0[q] = lo >= R ? 0ull : (R - lo >= kWave ? ~0ull : (1ull << (R - lo)) - 1ull);
-    L.lvl1[q] = 0ull;
+    L.lvl[q] = lo >= R ? 0ull : (R - lo >= kWave ? ~0ull : (1ull << (R - lo)) - 1ull);
+    L.lvl[TW + q] = 0ull;
   }
   for (int32_t q = tid; q < kRelPlanes * TW; q += NT) L.rel[q] = 0ull;
-  if (tid < 8) L.misc[tid] = tid == 1 ? INT_MAX : 0;
-  if (tid == 0) L.p0[0] = 0.0;
   const int32_t ns = wp.hdr[0];
   for (int32_t q = tid; q < ns; q += NT) L.cn[q] = (int8_t)wp.cn[q];
   for (int32_t q = tid; q < ns * kTierMax; q += NT) {
@@ -1328,515 +1748,26 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
       for (int64_t q = tid; q < (int64_t)R * S; q += NT) Xb[q] = 0;
     }
   }
+  // HW_ID bits 5:4 hold the SIMD of the wave
+  if (NW > 1 && lane == 0) simd_of[wid] = (int32_t)__builtin_amdgcn_s_getreg((1 << 11) | (4 << 6) | 4);
   __syncthreads();
-
-  // Every bid names a rank, which then serves its best bidder with a positive
-  // amount; so every open slot with a valid rank bids again in every round.
-  // A slot drops out once it is full or finds no valid rank (validity only
-  // ends).  The layout of 16-word rank sets (one problem per compute unit)
-  // and the 4-wave layout in its build for many problems per compute unit
-  // keep a list of the open slots, packed into the first waves each round,
-  // so that few waves issue the bid searches (there the search competes for
-  // issue slots), with each slot's bid state in LDS; the one-wave layout,
-  // the 4-wave layout with few problems per compute unit (a round is then a
-  // chain of latencies) and the largest slot counts keep each slot and its
-  // state with the thread that took it from the first round's list.  A
-  // round is two steps, one barrier each, with
-  // the list counts in two buffers by round parity and the list and the rank
-  // keys in one (every thread has read its entries before the barrier that
-  // precedes the rewrite; each rank's winner clears its key, and a bidder
-  // that reads the key after that sees 0, not its own key, and loses as it
-  // should):
-  //   X: each open slot bids and posts its key to the rank it bid for;
-  //   Y: the same thread moves tokens if its slot won, and keeps the slot
-  //      while it still plans tokens; a transfer marks the round, and a round
-  //      without one (no bid) ends the auction.
-  // Incremental bids.  A slot keeps, while the base count stays (an epoch),
-  // the first tier ts that holds a valid rank for it and a resume rank pos
-  // such that no valid rank of tier ts below pos is at the base count.  Both
-  // hold in later rounds: validity only ends and counts only rise.  So tiers
-  // before ts are empty, and the lowest base-count rank of tier ts at or
-  // after pos, when there is one, is the tier's fewest-services rank (score
-  // bonus - P0); the later tiers follow with the usual pruning.  Otherwise
-  // the full search runs from tier ts.  The bid rank becomes the next pos.
-  const double step = p.price_step;
-  const bool track = step > 0.0;  // counts order the prices; with step 0 all prices stay 0
+  if constexpr (NW > 1) {
+    // one wave goes on: on another SIMD in each of the workgroups that follow
+    // one another on a compute unit (any choice gives the same schedule)
+    const int want = (int)(blockIdx.x >> 8) & 3;
+    int it = 0;
+    for (int w = NW - 1; w >= 0; --w) it = simd_of[w] == want ? w : it;
+    if (__builtin_amdgcn_readfirstlane(wid) != it) return;
+  }
   const int64_t tmax = p.t_max > 0 ? p.t_max : (int64_t)S * (R + 1);
-  constexpr uint32_t kSlotMask = (1u << kItemSlotBits) - 1u, kExpMask = (1u << kItemExpertBits) - 1u;
-  // Slot state: resume rank (bits 0-10), first tier (11-12), then the
-  // epoch.  The packed layout keeps it in LDS in 16 bits beside the slot's
-  // list entry (same position, read together with it), with the epoch's
-  // parity (bit 13) and a valid bit (14): a listed slot's state is rewritten
-  // in every round it bids, and the base moves at most once per round, so a
-  // state read back is from the current epoch or the one before; a slot
-  // that takes over a group gets the state of the slot it replaces.
-  constexpr int kPosBits = 11, kTsBits = 2;
-  static_assert(TW * kWave < (1 << kPosBits) && kTierMax <= (1 << kTsBits), "slot state fields");
-  // pack the open slots into the first waves each round (several waves, at
-  // most two slots per thread: the LDS of four does not hold their states)
-  int32_t item[SPL];
-  uint32_t state[SPL];
-#pragma unroll
-  for (int i = 0; i < SPL; ++i) {
-    item[i] = i * NT + tid < sh_nw[1] ? L.work[i * NT + tid] : -1;
-    state[i] = 0xFFFFFFFFu;  // no epoch matches it
-  }
-  if constexpr (kPack) {
-    for (int32_t s = tid; s < S; s += NT) L.sstate[s] = 0;  // not valid
-    __syncthreads();  // the first round reads states other threads cleared
-  }
-  int64_t rounds = 0;
-  for (int64_t t = 1; t <= tmax; ++t) {
-    const int cur = (int)(t & 1), prv = cur ^ 1;
-    uint32_t* rk = L.rkey;
-    const int32_t maxc = sh_maxc;
-    const int32_t nplanes = maxc > 0 ? 32 - __builtin_clz((uint32_t)maxc) : 0;
-    const double P0 = L.p0[0];
-    const uint32_t epoch = (uint32_t)L.misc[6];
-    const int32_t nw = sh_nw[cur];
-    // When problems share a compute unit (up to eight at R = 256), the
-    // kernel ends with the last of them: the wave that holds a round's
-    // list takes an issue priority that grows with the list, so that the
-    // problems with more open slot groups (more work left) go first.  A
-    // problem alone on its compute unit, and the one-wave layout of the
-    // small batches, only pay for the extra instructions.
-    if (NT > kWave && wp.shared && wid == 0) {
-      if (nw >= 32) __builtin_amdgcn_s_setprio(3);
-      else if (nw >= 16) __builtin_amdgcn_s_setprio(2);
-      else if (nw >= 4) __builtin_amdgcn_s_setprio(1);
-      else __builtin_amdgcn_s_setprio(0);
-    }
-    if (kPack && tid == 0) sh_nw[prv] = 0;
-    // ---- X: bids --------------------------------------------------------------------------
-    int32_t bid[SPL], held[SPL];
-    uint32_t key[SPL];
-#pragma unroll
-    for (int i = 0; i < SPL; ++i) {
-      bid[i] = -1;
-      key[i] = 0;
-      held[i] = 0;
-      if constexpr (kPack) {
-        // the entry and its state are read together (states travel with
-        // the list entries); positions past the list are read and dropped
-        const int32_t q = i * NT + tid, qc = q < S ? q : 0;
-        const int32_t wq = L.work[qc];
-        const uint32_t sq = L.sstate[qc];
-        item[i] = q < nw ? wq : -1;
-        state[i] = sq;
-      }
-      const int32_t it = item[i];
-      if (it < 0) continue;
-      const int32_t s = it & kSlotMask, d = (it >> kItemSlotBits) & kExpMask;
-      const int32_t st = it >> (kItemSlotBits + kItemExpertBits);
-      // argmax over ranks holding tokens of the slot's expert of
-      // Bauct[r][host] - price[r], lowest rank on ties, by tiers
-      const int32_t nt = L.cn[st];
-      const uint64_t* vm = L.vmask + d * TW;
-      int32_t ts = 0, pos = 0;
-      const bool st_ok = kPack ? ((state[i] >> 14) & 1u) && ((state[i] >> 13) & 1u) == (epoch & 1u)
-                               : (state[i] >> (kPosBits + kTsBits)) == epoch;
-      if (st_ok) {
-        ts = (int32_t)((state[i] >> kPosBits) & ((1u << kTsBits) - 1u));
-        pos = (int32_t)(state[i] & ((1u << kPosBits) - 1u));
-      }
-      double bs = -INFINITY;
-      int32_t br = INT_MAX, bv = 0;
-      int32_t nts = -1, npos = R;  // the new state: first tier with a valid rank, its base-count rank
-      if constexpr (TW <= 4) {
-        // rank sets of at most 4 words live in registers; the tier data is
-        // read per tier (the registers of the capped builds are scarce)
-        uint64_t valid[TW];
-#pragma unroll
-        for (int w = 0; w < TW; ++w) valid[w] = vm[w];
-        // lowest valid rank of tier ti at the base count, at or after rank from
-        auto scan0 = [&](int32_t ti, int32_t from) {
-          const uint64_t* tm = L.cm + (st * kTierMax + ti) * TW;
-          int32_t hit = INT_MAX;
-#pragma unroll
-          for (int w = TW - 1; w >= 0; --w) {
-            uint64_t h = tm[w] & valid[w] & L.lvl0[w];
-            h = w < (from >> 6) ? 0ull : w == (from >> 6) ? h & (~0ull << (from & 63)) : h;
-            if (h) hit = w * kWave + __builtin_ctzll(h);
-          }
-          return hit;
-        };
-        // fewest services among the valid ranks of tier ti: the smallest
-        // relative code, then (all saturated) the smallest count; one plane
-        // per step; INT_MAX when the tier holds no valid rank
-        auto deep = [&](int32_t ti) {
-          const uint64_t* tm = L.cm + (st * kTierMax + ti) * TW;
-          uint64_t c[TW], m[TW];
-          uint64_t anyc = 0;
-#pragma unroll
-          for (int w = 0; w < TW; ++w) { c[w] = tm[w] & valid[w]; anyc |= c[w]; }
-          if (!anyc) return (int32_t)INT_MAX;
-          // no candidate is at the base count, so the lowest one a service
-          // above it, when there is one, has the fewest services
-          {
-            int32_t r1 = INT_MAX;
-#pragma unroll
-            for (int w = TW - 1; w >= 0; --w) {
-              const uint64_t h1 = c[w] & L.lvl1[w];
-              if (h1) r1 = w * kWave + __builtin_ctzll(h1);
-            }
-            if (r1 != INT_MAX) return r1;
-          }
-          bool sat = true;
-#pragma unroll 1
-          for (int j = kRelPlanes - 1; j >= 0; --j) {
-            uint64_t mm = 0;
-#pragma unroll
-            for (int w = 0; w < TW; ++w) { m[w] = c[w] & ~L.rel[j * TW + w]; mm |= m[w]; }
-            sat &= mm == 0ull;
-            if (mm) {
-#pragma unroll
-              for (int w = 0; w < TW; ++w) c[w] = m[w];
-            }
-          }
-          if (sat && track) {
-            for (int32_t j = nplanes - 1; j >= 0; --j) {
-              uint64_t mm = 0;
-#pragma unroll
-              for (int w = 0; w < TW; ++w) { m[w] = c[w] & ~L.planes[j * TW + w]; mm |= m[w]; }
-              if (mm) {
-#pragma unroll
-                for (int w = 0; w < TW; ++w) c[w] = m[w];
-              }
-            }
-          }
-          int32_t rr = INT_MAX;
-#pragma unroll
-          for (int w = TW - 1; w >= 0; --w)
-            if (c[w]) rr = w * kWave + __builtin_ctzll(c[w]);
-          return rr;
-        };
-        int32_t t0 = ts;
-        bool resume_fail = false;  // tier ts holds no valid rank at the base count
-        if (ts < nt) {
-          const int32_t h = scan0(ts, pos);
-          if (h != INT_MAX) {
-            bs = L.cv[st * kTierMax + ts] - P0;
-            br = h;
-            bv = L.cvr[st * kTierMax + ts];
-            nts = ts;
-            npos = h;
-            t0 = ts + 1;
-          } else {
-            resume_fail = true;
-          }
-        }
-        for (int32_t ti = t0; ti < nt; ++ti) {
-          const double v = L.cv[st * kTierMax + ti];
-          if (v - P0 < bs) break;  // no score in this tier or the next reaches bs
-          const int32_t h = resume_fail && ti == ts ? INT_MAX : scan0(ti, 0);
-          const bool at0 = h != INT_MAX;  // a candidate at the base count: its price is P0
-          const int32_t rr = at0 ? h : deep(ti);
-          if (rr == INT_MAX) continue;  // no valid rank in this tier
-          if (nts < 0) { nts = ti; npos = at0 ? h : R; }
-          const double sc = v - (at0 ? P0 : L.price[rr]);
-          if (sc > bs || (sc == bs && rr < br)) { bs = sc; br = rr; bv = L.cvr[st * kTierMax + ti]; }
-        }
-      } else {
-        const uint32_t vw = L.vwords[d];
-        // the structure's tier bonuses, bonus ranks and words, loaded once
-        // (16-byte loads); the tier loop is unrolled so that they stay in
-        // registers
-        double cvv[kTierMax];
-        int32_t cvrr[kTierMax];
-        uint32_t cww[kTierMax];
-        {
-          const double2* cv2 = reinterpret_cast<const double2*>(L.cv + st * kTierMax);
-          const double2 a = cv2[0], b2 = cv2[1];
-          cvv[0] = a.x; cvv[1] = a.y; cvv[2] = b2.x; cvv[3] = b2.y;
-          const int4 r4 = *reinterpret_cast<const int4*>(L.cvr + st * kTierMax);
-          cvrr[0] = r4.x; cvrr[1] = r4.y; cvrr[2] = r4.z; cvrr[3] = r4.w;
-          const uint4 w4 = *reinterpret_cast<const uint4*>(L.cw + st * kTierMax);
-          cww[0] = w4.x; cww[1] = w4.y; cww[2] = w4.z; cww[3] = w4.w;
-        }
-        // lowest valid rank of a tier at the base count, at or after rank
-        // from: the tier's words with valid ranks, ascending, one per step
-        auto scan0 = [&](const uint64_t* tm, uint32_t words, int32_t from) {
-          const int32_t wf = from >> 6;
-          for (uint32_t ws = wf < 32 ? words & (~0u << wf) : 0u; ws; ws &= ws - 1u) {
-            const int w = __builtin_ctz(ws);
-            uint64_t h = tm[w] & vm[w] & L.lvl0[w];
-            if (w == wf) h &= ~0ull << (from & 63);
-            if (h) return w * kWave + __builtin_ctzll(h);
-          }
-          return (int32_t)INT_MAX;
-        };
-        // fewest services among the valid ranks of a tier: the smallest
-        // relative code over its words with valid ranks, up to four words per
-        // group (a bit-sliced minimum within the group; a group replaces the
-        // best only with a smaller code, so equal codes keep the lower
-        // words), then (all saturated) the bit-plane search over the full
-        // counts; INT_MAX when the tier holds no valid rank
-        auto deep = [&](const uint64_t* tm, uint32_t words) {
-          int32_t rr = INT_MAX;
-          uint32_t best = kRelMax + 1, cand = 0;
-          for (uint32_t wl = words; wl;) {
-            int wi[4];
-            uint64_t c[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              wi[u] = wl ? __builtin_ctz(wl) : -1;
-              wl &= wl - 1u;
-            }
-            uint64_t pl[kRelPlanes][4], l1[4];
-            uint64_t any = 0;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const int w = wi[u] < 0 ? 0 : wi[u];
-              c[u] = wi[u] < 0 ? 0ull : tm[w] & vm[w];
-              any |= c[u];
-              cand |= (c[u] != 0ull ? 1u : 0u) << w;
-              l1[u] = L.lvl1[w];
-#pragma unroll
-              for (int j = 0; j < kRelPlanes; ++j) pl[j][u] = L.rel[j * TW + w];
-            }
-            if (!any) continue;
-            // no candidate is at the base count, so a candidate one service
-            // above it has the fewest services: the first group (words
-            // ascending) that holds one gives the lowest such rank
-            {
-              int32_t r1 = INT_MAX;
-#pragma unroll
-              for (int u = 3; u >= 0; --u) {
-                const uint64_t h1 = c[u] & l1[u];
-                if (h1) r1 = wi[u] * kWave + __builtin_ctzll(h1);
-              }
-              if (r1 != INT_MAX) return r1;
-            }
-            uint32_t code = 0;
-#pragma unroll
-            for (int j = kRelPlanes - 1; j >= 0; --j) {
-              uint64_t m[4], mm = 0;
-#pragma unroll
-              for (int u = 0; u < 4; ++u) { m[u] = c[u] & ~pl[j][u]; mm |= m[u]; }
-              if (mm) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) c[u] = m[u];
-              } else {
-                code |= 1u << j;
-              }
-            }
-            if (code < best) {
-              best = code;
-#pragma unroll
-              for (int u = 3; u >= 0; --u)
-                if (c[u]) rr = wi[u] * kWave + __builtin_ctzll(c[u]);
-            }
-          }
-          if (best == kRelMax && track) {
-            // a word's minimum count is the planes where no candidate remained
-            rr = INT_MAX;
-            uint32_t cmin = 0xFFFFFFFFu;
-            for (uint32_t ws = cand; ws; ws &= ws - 1) {
-              const int w = __builtin_ctz(ws);
-              uint64_t x = tm[w] & vm[w];
-              uint32_t mn = 0;
-              for (int32_t j = nplanes - 1; j >= 0; --j) {
-                const uint64_t m = x & ~L.planes[j * TW + w];
-                if (m) x = m;
-                else mn |= 1u << j;
-              }
-              if (mn < cmin) {  // words ascend: equal counts keep the lower rank
-                cmin = mn;
-                rr = w * kWave + __builtin_ctzll(x);
-              }
-            }
-          }
-          return rr;
-        };
-        bool resume_fail = false;  // tier ts holds no valid rank at the base count
-        int32_t t0 = ts;
-        if (ts < nt) {
-          // the register arrays indexed by ts without dynamic indexing
-          const uint32_t cw_ts = ts == 0 ? cww[0] : ts == 1 ? cww[1] : ts == 2 ? cww[2] : cww[3];
-          const int32_t h = scan0(L.cm + (st * kTierMax + ts) * TW, cw_ts & vw, pos);
-          if (h != INT_MAX) {
-            bs = (ts == 0 ? cvv[0] : ts == 1 ? cvv[1] : ts == 2 ? cvv[2] : cvv[3]) - P0;
-            br = h;
-            bv = ts == 0 ? cvrr[0] : ts == 1 ? cvrr[1] : ts == 2 ? cvrr[2] : cvrr[3];
-            nts = ts;
-            npos = h;
-            t0 = ts + 1;
-          } else {
-            resume_fail = true;
-          }
-        }
-#pragma unroll
-        for (int ti = 0; ti < kTierMax; ++ti) {
-          if (ti < t0) continue;
-          if (ti >= nt) break;
-          const double v = cvv[ti];
-          if (v - P0 < bs) break;  // no score in this tier or the next reaches bs
-          const uint32_t cwt = cww[ti] & vw;
-          if (!cwt) continue;  // no valid rank in this tier
-          const uint64_t* tm = L.cm + (st * kTierMax + ti) * TW;
-          const int32_t h = resume_fail && ti == ts ? INT_MAX : scan0(tm, cwt, 0);
-          const bool at0 = h != INT_MAX;  // a candidate at the base count: its price is P0
-          const int32_t rr = at0 ? h : deep(tm, cwt);
-          if (rr == INT_MAX) continue;  // no valid rank in this tier
-          if (nts < 0) { nts = ti; npos = at0 ? h : R; }
-          const double sc = v - (at0 ? P0 : L.price[rr]);
-          if (sc > bs || (sc == bs && rr < br)) { bs = sc; br = rr; bv = cvrr[ti]; }
-        }
-      }
-      if (nts >= 0) {
-        if constexpr (kPack) {
-          state[i] = (uint32_t)npos | ((uint32_t)nts << kPosBits) | ((epoch & 1u) << 13) | (1u << 14);
-        } else {
-          state[i] = (uint32_t)npos | ((uint32_t)nts << kPosBits) | (epoch << (kPosBits + kTsBits));
-        }
-      }
-      if (br != INT_MAX) {
-        bid[i] = br;
-        key[i] = ((uint32_t)bv << 16) | (uint32_t)(0xFFFF - s);  // bonus, then lowest slot
-        held[i] = np[(int64_t)d * R + br];
-        atomicMax(&rk[br], key[i]);
-      }
-    }
-    // the barrier orders the keys (LDS); the token loads above complete on
-    // their own before Y uses them
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    // ---- Y: transfers -----------------------------------------------------------------------
-    // the flags of the next round (read by every thread before the barrier above)
-    if (tid == 0) { L.misc[2 + prv] = 0; L.misc[4 + prv] = 0; }
-#pragma unroll
-    for (int i = 0; i < SPL; ++i) {
-      const int32_t r = bid[i];
-      // a slot without a bid has no valid rank left (validity only ends)
-      bool keep = r >= 0;
-      int32_t succ = -1;  // packed layout: the slot that takes over a filled slot's group
-      if (keep && rk[r] == key[i]) {
-        const int32_t s = item[i] & kSlotMask, d = (item[i] >> kItemSlotBits) & kExpMask;
-        // the winner's reads first, so that they share one LDS round trip
-        // (the stores below may alias them as far as the compiler knows)
-        int32_t a = L.amt[s];
-        const double pr = L.price[r];
-        const int32_t c0 = L.cnt[r], base = L.misc[0];
-        const int32_t gn = kPack ? (int32_t)gnext[s] : -1;
-        rk[r] = 0u;  // the rank's key is cleared for the next round
-        const uint64_t bit = 1ull << (r & 63);
-        // A winner always moves tokens (x > 0): its rank held tokens of the
-        // slot's expert when the slot bid (a valid rank), one slot at most is
-        // served per rank and round, and a listed slot still plans tokens.  So
-        // the price and count updates come first, while the token count loaded
-        // with the bid (device memory) is still on its way.
-        L.misc[4 + cur] = 1;
-        L.price[r] = pr + step;
-        if (track) {
-          const int32_t c1 = c0 + 1;
-          L.cnt[r] = c1;
-          if (c1 > maxc) atomicMax(&sh_maxc, c1);  // a new largest count (rare)
-          for (uint32_t flip = (uint32_t)(c0 ^ c1); flip; flip &= flip - 1)
-            atomicXor(reinterpret_cast<unsigned long long*>(&L.planes[__builtin_ctz(flip) * TW + (r >> 6)]), bit);
-          // the relative code rises by one (below saturation); a word of the
-          // base-count set that empties is flagged for the round's end
-          const int32_t k0 = c0 - base;
-          if (k0 < kRelMax)
-            for (uint32_t flip = (uint32_t)(k0 ^ (k0 + 1)); flip; flip &= flip - 1)
-              atomicXor(reinterpret_cast<unsigned long long*>(&L.rel[__builtin_ctz(flip) * TW + (r >> 6)]), bit);
-          if (k0 == 0) {
-            const uint64_t old = atomicXor(reinterpret_cast<unsigned long long*>(&L.lvl0[r >> 6]), bit);
-            if (old == bit) L.misc[2 + cur] = 1;
-          }
-          // the rank enters (code 0 -> 1) or leaves (1 -> 2) the set one above the base
-          if (k0 == 0 || k0 == 1) atomicXor(reinterpret_cast<unsigned long long*>(&L.lvl1[r >> 6]), bit);
-        }
-        const int32_t have = held[i];
-        const int32_t x = have < a ? have : a;
-        Xb[(int64_t)r * S + s] = x;
-        np[(int64_t)d * R + r] = have - x;
-        a -= x;
-        L.amt[s] = a;
-        keep = a > 0;
-        if (!keep) succ = gn;
-        if (have - x <= 0) {
-          const uint64_t old = atomicAnd(reinterpret_cast<unsigned long long*>(&L.vmask[d * TW + (r >> 6)]), ~bit);
-          if constexpr (TW > 4)  // the word list only guides the per-word search
-            if ((old & ~bit) == 0ull) atomicAnd(&L.vwords[d], ~(1u << (r >> 6)));
-        }
-      }
-      if constexpr (kPack) {
-        int32_t next = item[i];
-        if (succ >= 0) {  // takes the filled slot's place and its bid state
-          next = (next & ~(int32_t)kSlotMask) | succ;
-          keep = true;
-        }
-        const uint16_t nst = (uint16_t)state[i];
-        if (nw <= kWave) {
-          // the round's whole list sits on wave 0 (entries 0 .. nw-1), so the
-          // next one is compacted there without an atomic
-          if (i == 0 && wid == 0) {
-            const uint64_t m = __ballot(keep);
-            if (keep) {
-              const int32_t pos = (int32_t)__popcll(m & ((1ull << lane) - 1ull));
-              L.work[pos] = next;
-              L.sstate[pos] = nst;
-            }
-            if (lane == 0) sh_nw[prv] = (int32_t)__popcll(m);
-          }
-        } else {
-          const int32_t pos = list_append(keep, next, L.work, &sh_nw[prv]);
-          if (keep) L.sstate[pos] = nst;
-        }
-      } else if (!keep) {
-        item[i] = -1;
-      }
-    }
-    __syncthreads();
-    if (!L.misc[4 + cur]) break;  // no bid this round: the state is final
-    rounds = t;
-    bool l0_empty = false;
-    if (track && L.misc[2 + cur]) {
-      l0_empty = true;
-#pragma unroll
-      for (int w = 0; w < TW; ++w) l0_empty &= L.lvl0[w] == 0ull;
-    }
-    if (l0_empty) {
-      // Every rank has left the base count: the base moves to the new fewest
-      // services and the relative codes are rebuilt from the counts.  Rank r
-      // is thread r, so wave w builds word w; p0 takes the price of a rank at
-      // the new base (every such rank has the same price).
-      const int32_t mine = tid < R ? L.cnt[tid] : INT_MAX;
-      const int32_t wmin = -wave_max_i32(-mine);
-      if (lane == 0) atomicMin(&L.misc[1], wmin);
-      __syncthreads();
-      const int32_t nb = L.misc[1];
-      const int32_t kr = tid < R ? min(L.cnt[tid] - nb, kRelMax) : -1;
-      const uint64_t m0 = __ballot(kr == 0), m1 = __ballot(kr == 1);
-      if (lane == 0 && wid < TW) {
-        L.lvl0[wid] = m0;
-        L.lvl1[wid] = m1;
-      }
-#pragma unroll
-      for (int j = 0; j < kRelPlanes; ++j) {
-        const uint64_t m = __ballot(kr > 0 && ((kr >> j) & 1));
-        if (lane == 0 && wid < TW) L.rel[j * TW + wid] = m;
-      }
-      if (kr == 0) L.p0[0] = L.price[tid];
-      __syncthreads();
-      if (tid == 0) { L.misc[0] = nb; L.misc[1] = INT_MAX; L.misc[6] += 1; }
-      __syncthreads();
-    }
-  }
+  const int64_t rounds = auction_rounds<CF>(L, gnext, np, Xb, R, S, sh_nw, p.price_step, tmax);
 
   int64_t left = 0;
   // (a slot without an expert plans 0 tokens; the slot experts may hold the
   // bid groups' links by now)
-  for (int32_t s = tid; s < S; s += NT) left += L.amt[s];
-  left = wave_sum_i64(left);
-  __syncthreads();
-  if (tid == 0) sh_sum = 0;
-  __syncthreads();
-  if (lane == 0) atomicAdd(&sh_sum, (unsigned long long)left);
-  __syncthreads();
-  if (tid == 0) {
-    const int64_t tot = (int64_t)sh_sum;
+  for (int32_t s = lane; s < S; s += kWave) left += L.amt[s];
+  const int64_t tot = wave_sum_i64(left);
+  if (lane == 0) {
     p.unfilled[b] = tot;
     if (p.rounds_used) { p.rounds_used[2 * b] = used2; p.rounds_used[2 * b + 1] = (int32_t)rounds; }
     if (p.status) p.status[b] = tot > 0 ? TAOT_ST_UNFILLED : 0u;
@@ -1891,12 +1822,12 @@ SchWs carve_sched(void* ws, int32_t B, int32_t R, int32_t E, int32_t K) {
   return w;
 }
 
-template <class CF, int SPL, int WPE>
+template <class CF, int WPE>
 taot_status launch_lds_kernel(const LdsParams& wp, int32_t B, size_t lds, hipStream_t stream) {
-  if (lds > 65536 && hipFuncSetAttribute((const void*)schedule_lds_kernel<CF, SPL, WPE>,
+  if (lds > 65536 && hipFuncSetAttribute((const void*)schedule_lds_kernel<CF, WPE>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return TAOT_ERR_LAUNCH;
-  hipLaunchKernelGGL((schedule_lds_kernel<CF, SPL, WPE>), dim3((unsigned)B), dim3(CF::kT), lds, stream, wp);
+  hipLaunchKernelGGL((schedule_lds_kernel<CF, WPE>), dim3((unsigned)B), dim3(CF::kT), lds, stream, wp);
   return hipGetLastError() == hipSuccess ? TAOT_OK : TAOT_ERR_LAUNCH;
 }
 
@@ -1934,20 +1865,12 @@ taot_status launch_lds_path(const SchParams& p, const SchWs& w, int32_t B, int32
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     return TAOT_ERR_LAUNCH;
-  const LdsParams wp{p, w.sidx, w.cn, w.cv, w.cvr, w.cw, w.cm, w.hdr, w.fallback, w.nprime, NEC, B > cus ? 1 : 0};
+  const LdsParams wp{p, w.sidx, w.cn, w.cv, w.cvr, w.cw, w.cm, w.hdr, w.fallback, w.nprime, NEC};
   taot_status st;
   // a batch of more problems than fit six to a compute unit takes the
   // register-capped build, which can hold CF::kWavesPerEU per SIMD
   const bool cap = (int64_t)B > (int64_t)6 * cus;
-  if (S <= CF::kT)
-    st = cap ? launch_lds_kernel<CF, 1, CF::kWavesPerEU>(wp, B, slds, stream)
-             : launch_lds_kernel<CF, 1, 1>(wp, B, slds, stream);
-  else if (S <= 2 * CF::kT)
-    st = cap ? launch_lds_kernel<CF, 2, CF::kWavesPerEU>(wp, B, slds, stream)
-             : launch_lds_kernel<CF, 2, 1>(wp, B, slds, stream);
-  else
-    st = cap ? launch_lds_kernel<CF, 4, CF::kWavesPerEU>(wp, B, slds, stream)
-             : launch_lds_kernel<CF, 4, 1>(wp, B, slds, stream);
+  st = cap ? launch_lds_kernel<CF, CF::kWavesPerEU>(wp, B, slds, stream) : launch_lds_kernel<CF, 1>(wp, B, slds, stream);
   launched = st == TAOT_OK;
   return st;
 }
