@@ -563,6 +563,7 @@ struct LdsSmall {
   static constexpr int kMaxS = 1024; // R*K
   static constexpr int kNEC = 128;   // candidate experts (spill > 0) in LDS
   static constexpr int kWavesPerEU = 8;  // large batches: eight problems per compute unit (20 KB of LDS each at R = 256, K = 2)
+  static constexpr int kG = 2;       // bid groups per lane that the auction keeps in registers
 };
 struct LdsTiny {
   static constexpr int kT = 64;      // one wave per problem: its barriers cost next to nothing
@@ -573,6 +574,7 @@ struct LdsTiny {
   static constexpr int kMaxS = 256;
   static constexpr int kNEC = 128;
   static constexpr int kWavesPerEU = 8;
+  static constexpr int kG = 1;
 };
 struct LdsLarge {
   static constexpr int kT = 1024;
@@ -583,6 +585,7 @@ struct LdsLarge {
   static constexpr int kMaxS = 4096;
   static constexpr int kNEC = 1024;
   static constexpr int kWavesPerEU = 1;  // one problem per compute unit in any case
+  static constexpr int kG = 4;
 };
 // The count window's rebuild takes rank r on thread r (wave w builds word w).
 static_assert(LdsSmall::kT == LdsSmall::kTW * kWave && LdsTiny::kT == LdsTiny::kTW * kWave &&
@@ -886,8 +889,23 @@ __host__ __device__ inline LdsState<CF> carve_lds(char* base, int32_t R, int32_t
   return w;
 }
 
+// What the matching kernel leaves for the auction's: per problem a header
+// (listed groups, or -1: not for the auction; Phase-2 iterations; slot
+// experts), tokens planned, next slots of the bid groups, list items [S]; most
+// tokens and valid words [DC], valid ranks [DC][TW] of the slot experts.
+struct Handoff {
+  int4* hdr;        // [B]
+  int32_t* amt;     // [B][S]
+  int32_t* work;    // [B][S]
+  int16_t* gnext;   // [B][S]
+  int32_t* nmax;    // [B][DC]
+  uint32_t* vwords; // [B][DC]
+  uint64_t* vmask;  // [B][DC][TW]
+};
+
 struct LdsParams {
   SchParams s;
+  Handoff h;
   const int32_t* sidx;   // [R] host -> tier structure
   const int32_t* cn;     // [SC] tiers per structure
   const double* cv;      // [SC][kTierMax] tier bonuses, descending
@@ -948,8 +966,13 @@ __device__ __forceinline__ int32_t wave_max_i32(int32_t v) {
   return max((int32_t)r32[0], (int32_t)r32[1]);
 }
 
-// The rounds of the auction, on one wave of the problem's workgroup; returns
-// how many ran.
+// Where word w of row `row` of a table of rank sets stands in its row.
+template <int TW>
+__device__ __forceinline__ int set_word(int32_t row, int w) {
+  return w ^ (row & (TW - 1));
+}
+
+// The rounds of the auction, on one wave; returns how many ran.
 //
 // Every bid names a rank, which then serves its best bidder with a positive
 // amount; so every group with an open slot and a valid rank bids again in
@@ -962,8 +985,8 @@ __device__ __forceinline__ int32_t wave_max_i32(int32_t v) {
 // What bounds it: the rounds follow from one another (about 1200 at R = 256,
 // 10000 at R = 1024) and hold few transfers (4 to 6) for the list they walk,
 // so a round costs its chain of latencies.  One wave runs it without a barrier,
-// as the LDS operations of a wave stay in order; lists of up to 64 groups stay
-// in registers, a group to a lane, longer ones are walked 64 at a time.
+// as the LDS operations of a wave stay in order; lists of up to 64 kG groups
+// stay in registers, kG to a lane, longer ones are walked 64 at a time.
 //
 // Incremental bids.  Within an epoch (while the base count stays) a group keeps
 // its first tier ts that holds a valid rank, the fewest services lev (above the
@@ -994,7 +1017,7 @@ template <class CF>
 __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const int16_t* gnext, int32_t* np,
                                                   int32_t* Xb, int32_t R, int32_t S, int32_t nw, double step,
                                                   int64_t tmax) {
-  constexpr int TW = CF::kTW;
+  constexpr int TW = CF::kTW, G = CF::kG;
   constexpr int32_t kSlotMask = (1 << kItemSlotBits) - 1, kExpMask = (1 << kItemExpertBits) - 1;
   constexpr int32_t kItemBits = 26, kItemMask = (1 << kItemBits) - 1;
   constexpr int32_t kStructMask = (1 << (kItemBits - kItemSlotBits - kItemExpertBits)) - 1;
@@ -1009,6 +1032,11 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
   uint32_t epoch = 0;             // parity
   bool planes_on = false;         // the planes of the full counts are kept from their first use on
 
+  // word w of tier e = structure * kTierMax + tier, and of expert d's valid
+  // ranks (rows of TW words, rotated so that the same word of different rows
+  // does not sit in the same banks)
+  auto tier_word = [&](int32_t e, int w) { return L.cm[e * TW + set_word<TW>(e / kTierMax, w)]; };
+  auto valid_word = [&](int32_t d, int w) { return L.vmask[d * TW + set_word<TW>(d, w)]; };
   auto expert = [](int32_t it) { return (it >> kItemSlotBits) & kExpMask; };
   auto structure = [](int32_t it) { return (it >> (kItemSlotBits + kItemExpertBits)) & kStructMask; };
   // ranks of word w with exactly lev services above the base count
@@ -1028,7 +1056,6 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
   // saturated and the count planes are off.
   auto search = [&](int32_t it, uint32_t state, bool& stuck) {
     const int32_t d = expert(it), st = structure(it);
-    const uint64_t* vm = L.vmask + d * TW;
     const int32_t nt = L.cn[st];
     const uint32_t vw = TW > 4 ? L.vwords[d] : ~0u;
     const int32_t ts = (int32_t)(state >> 4) & 3;
@@ -1039,8 +1066,8 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
     for (int32_t ti = ts; ti < nt; ++ti) {
       const double v = L.cv[st * kTierMax + ti];
       if (found && v - P0 < bs) break;  // no score in this tier or the next reaches bs
-      const uint64_t* tm = L.cm + (st * kTierMax + ti) * TW;
-      const uint32_t words = L.cw[st * kTierMax + ti] & vw;
+      const int32_t e = st * kTierMax + ti;
+      const uint32_t words = L.cw[e] & vw;
       const bool resume = same && ti == ts;
       const uint32_t lev = resume ? (state >> 6) & 15u : 0u;
       int32_t rr = -1;
@@ -1050,7 +1077,7 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
       if (lev < 2u)
         for (uint32_t ws = resume ? words & (~0u << (state & 15u)) : words; ws; ws &= ws - 1u) {
           const int w = __builtin_ctz(ws);
-          const uint64_t c = tm[w] & vm[w], h = c & L.lvl[lev * TW + w];
+          const uint64_t c = tier_word(e, w) & valid_word(d, w), h = c & L.lvl[lev * TW + w];
           if (h) {
             rr = w * kWave + __builtin_ctzll(h);
             win = c;
@@ -1062,7 +1089,7 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
         uint32_t best = kRelMax + 1;
         for (uint32_t ws = words; ws; ws &= ws - 1u) {
           const int w = __builtin_ctz(ws);
-          const uint64_t all = tm[w] & vm[w];
+          const uint64_t all = tier_word(e, w) & valid_word(d, w);
           uint64_t c = all, p[kRelPlanes];
 #pragma unroll
           for (int j = 0; j < kRelPlanes; ++j) p[j] = L.rel[j * TW + w];
@@ -1088,7 +1115,7 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
           uint32_t cmin = 0xFFFFFFFFu;
           for (uint32_t ws = planes_on ? words : 0u; ws; ws &= ws - 1u) {
             const int w = __builtin_ctz(ws);
-            uint64_t x = tm[w] & vm[w];
+            uint64_t x = tier_word(e, w) & valid_word(d, w);
             if (!x) continue;
             uint32_t mn = 0;
             for (int32_t j = CF::kPL - 1; j >= 0; --j) {
@@ -1167,7 +1194,7 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
   auto drained = [&](int32_t d, int32_t r) {
     const unsigned long long bit = 1ull << (r & 63);
     const int w = r >> 6;
-    const uint64_t old = atomicAnd(reinterpret_cast<unsigned long long*>(&L.vmask[d * TW + w]), ~bit);
+    const uint64_t old = atomicAnd(reinterpret_cast<unsigned long long*>(&L.vmask[d * TW + set_word<TW>(d, w)]), ~bit);
     if constexpr (TW > 4)  // the word list only guides the search
       if ((old & ~bit) == 0ull) atomicAnd(&L.vwords[d], ~(1u << w));
   };
@@ -1201,7 +1228,7 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
   int64_t t = 1;
   // ---- lists longer than a wave: entries and states in LDS -----------------------------
   int32_t active = nw;
-  for (; t <= tmax && nw > kWave; ++t) {
+  for (; t <= tmax && nw > G * kWave; ++t) {
     // X: bids
     int32_t nit = lane < nw ? L.work[lane] : -1;
     uint32_t nst = lane < nw ? L.sstate[lane] : 0u;
@@ -1217,7 +1244,7 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
       if (it >= 0 && (b.state & kHas) != 0u && (b.state >> 11) == epoch) {
         const int32_t d = expert(it);
         const int w = (int)(b.state & 15u), e = structure(it) * kTierMax + (int)((b.state >> 4) & 3u);
-        const uint64_t h = L.cm[e * TW + w] & L.vmask[d * TW + w] & level((b.state >> 6) & 15u, w);
+        const uint64_t h = tier_word(e, w) & valid_word(d, w) & level((b.state >> 6) & 15u, w);
         b.v = L.cvr[e];
         if (h) b.r = w * kWave + __builtin_ctzll(h);
       }
@@ -1285,7 +1312,7 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
     }
     if (have_n > 0) transfers();
     if (track && base_left == 0) rebase();
-    if (active <= nw - kWave || active <= kWave) {
+    if (active <= nw - kWave) {
       // a group of lanes less will do: the list closes up in place (an entry
       // moves to its own place or a lower one)
       int32_t kept = 0;
@@ -1304,96 +1331,264 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
       nw = kept;
     }
   }
-  // ---- a group per lane, in registers ----------------------------------------------------
-  int32_t it = lane < nw ? L.work[lane] : -1;
-  Bid b{-1, 0, 0u, 0ull};
-  int32_t a = 0, most = 0;   // tokens planned; the most a rank can hold
-  int32_t pr = -1, pv = 0;   // a transfer in flight: its rank and what the rank held
-  if (it >= 0) {
-    it &= kItemMask;
-    b.state = L.sstate[lane] & kStateMask & ~kHas;  // (win is not known)
-    a = L.amt[it & kSlotMask];
-    most = nmax[expert(it)];
-  }
-  auto book = [&]() {  // the transfer in flight
-    Xb[(int64_t)pr * S + (it & kSlotMask)] = pv;
-    a -= pv;
-    pr = -1;
-  };
-  for (; t <= tmax; ++t) {
-    int32_t r = -1;
-    if (it >= 0 && (b.state & kHas) != 0u && (b.state >> 11) == epoch) {
-      const int w = (int)(b.state & 15u);
-      const uint64_t h = b.win & level((b.state >> 6) & 15u, w);
-      if (h) r = w * kWave + __builtin_ctzll(h);
+  // ---- up to G groups per lane, in registers ------------------------------------------------
+  while (t <= tmax) {
+    const int32_t sets = (nw + kWave - 1) / kWave;  // in use; the list closes up when one less will do
+    int32_t it[G], a[G], most[G];  // entry, tokens planned, the most a rank can hold
+    int32_t pr[G], pv[G];          // a transfer in flight: its rank and what the rank held
+    Bid b[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int32_t q = g * kWave + lane;
+      it[g] = q < nw ? L.work[q] : -1;
+      b[g] = Bid{-1, 0, 0u, 0ull};
+      a[g] = most[g] = pv[g] = 0;
+      pr[g] = -1;
+      if (it[g] >= 0) {
+        it[g] &= kItemMask;
+        b[g].state = L.sstate[q] & kStateMask & ~kHas;  // (win is not known)
+        a[g] = L.amt[it[g] & kSlotMask];
+        most[g] = nmax[expert(it[g])];
+      }
     }
-    const bool need = it >= 0 && r < 0;
-    if (__ballot(need) != 0) {
-      search_all(need, it, b);
-      if (need) {
-        r = b.r;
-        if (r < 0) {  // no valid rank is left
-          if (pr >= 0) book();
-          L.amt[it & kSlotMask] = a;
-          it = -1;
+    auto book = [&](int g) {  // the transfer in flight
+      Xb[(int64_t)pr[g] * S + (it[g] & kSlotMask)] = pv[g];
+      a[g] -= pv[g];
+      pr[g] = -1;
+    };
+    bool done = false;
+    for (; t <= tmax; ++t) {
+      int32_t r[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        r[g] = -1;
+        if (g >= sets) continue;
+        const bool ok = it[g] >= 0 && (b[g].state & kHas) != 0u && (b[g].state >> 11) == epoch;
+        const int w = (int)(b[g].state & 15u);
+        const uint32_t lev = (b[g].state >> 6) & 15u;
+        uint64_t m = L.lvl[(lev != 0u ? TW : 0) + w];
+        if (__ballot(ok && lev >= 2u) != 0)
+          if (lev >= 2u) m = level(lev, w);
+        const uint64_t h = b[g].win & m;
+        if (ok && h != 0ull) r[g] = w * kWave + __builtin_ctzll(h);
+      }
+      int32_t live = 0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if (g >= sets) continue;
+        const bool need = it[g] >= 0 && r[g] < 0;
+        if (__ballot(need) != 0) {
+          search_all(need, it[g], b[g]);
+          if (need) {
+            r[g] = b[g].r;
+            if (r[g] < 0) {  // no valid rank is left
+              if (pr[g] >= 0) book(g);
+              L.amt[it[g] & kSlotMask] = a[g];
+              it[g] = -1;
+            }
+          }
+        }
+        live += (int32_t)__popcll(__ballot(it[g] >= 0));
+      }
+      if (live == 0) {  // no bid: the state is final
+        done = true;
+        break;
+      }
+      uint32_t key[G], k[G];
+      int32_t c0[G];
+      double price[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        key[g] = ((uint32_t)b[g].v << 16) | (uint32_t)(0xFFFF - (it[g] & kSlotMask));
+        if (g < sets && it[g] >= 0) atomicMax(&rk[r[g]], key[g]);
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {  // (the rank's count and price come with its key)
+        if (g >= sets) continue;
+        const int32_t rr = it[g] >= 0 ? r[g] : 0;
+        k[g] = *(volatile uint32_t*)&rk[rr];
+        c0[g] = *(volatile int32_t*)&L.cnt[rr];
+        price[g] = *(volatile double*)&L.price[rr];
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if (g >= sets) continue;
+        const bool won = it[g] >= 0 && k[g] == key[g];
+        if (__ballot(won) == 0) continue;
+        bool left_base = false;
+        if (won) {
+          if (pr[g] >= 0) book(g);
+          pv[g] = np[(int64_t)expert(it[g]) * R + r[g]];
+          pr[g] = r[g];
+          left_base = serve(r[g], c0[g], price[g]);
+        }
+        base_left -= (int32_t)__popcll(__ballot(left_base));
+        const bool wait = won && a[g] <= most[g];  // the slot may fill
+        if (won && !wait) drained(expert(it[g]), r[g]);
+        if (__ballot(wait) != 0) {
+          if (wait) {
+            const int32_t d = expert(it[g]), s = it[g] & kSlotMask, have = pv[g];
+            if (have <= a[g]) drained(d, r[g]);
+            else np[(int64_t)d * R + r[g]] = have - a[g];
+            pv[g] = have < a[g] ? have : a[g];
+            book(g);
+            if (a[g] == 0) {
+              const int32_t gn = gnext[s];
+              L.amt[s] = 0;
+              it[g] = gn >= 0 ? (it[g] & ~kSlotMask) | gn : -1;
+              if (gn >= 0) a[g] = L.amt[gn];
+            }
+          }
         }
       }
-    }
-    if (__ballot(it >= 0) == 0) break;  // no bid: the state is final
-    const uint32_t key = ((uint32_t)b.v << 16) | (uint32_t)(0xFFFF - (it & kSlotMask));
-    bool won = false, left_base = false;
-    if (it >= 0) {
-      atomicMax(&rk[r], key);
-      // (the rank's count and price come with the key)
-      const uint32_t k = *(volatile uint32_t*)&rk[r];
-      const int32_t c0 = *(volatile int32_t*)&L.cnt[r];
-      const double price = *(volatile double*)&L.price[r];
-      won = k == key;
-      if (won) {
-        if (pr >= 0) book();
-        pv = np[(int64_t)expert(it) * R + r];
-        pr = r;
-        left_base = serve(r, c0, price);
+      if (track && base_left == 0) rebase();
+      if (sets > 1 && live <= kWave * (sets - 1)) {
+        ++t;
+        break;
       }
     }
-    base_left -= (int32_t)__popcll(__ballot(left_base));
-    const bool wait = won && a <= most;  // the slot may fill
-    if (won && !wait) drained(expert(it), r);
-    if (__ballot(wait) != 0) {
-      if (wait) {
-        const int32_t d = expert(it), s = it & kSlotMask, have = pv;
-        if (have <= a) drained(d, r);
-        else np[(int64_t)d * R + r] = have - a;
-        pv = have < a ? have : a;
-        book();
-        if (a == 0) {
-          const int32_t gn = gnext[s];
-          L.amt[s] = 0;
-          it = gn >= 0 ? (it & ~kSlotMask) | gn : -1;
-          if (gn >= 0) a = L.amt[gn];
-        }
+    int32_t kept = 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (it[g] >= 0) {
+        if (pr[g] >= 0) book(g);
+        L.amt[it[g] & kSlotMask] = a[g];
       }
+      const uint64_t m = __ballot(it[g] >= 0);
+      const int32_t to = kept + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+      if (it[g] >= 0) {
+        L.work[to] = it[g];
+        L.sstate[to] = (uint16_t)b[g].state;
+      }
+      kept += (int32_t)__popcll(m);
     }
-    if (track && base_left == 0) rebase();
-  }
-  if (it >= 0) {
-    if (pr >= 0) book();
-    L.amt[it & kSlotMask] = a;
+    if (done) break;
+    nw = kept;
   }
   return t - 1;
 }
 
-// One problem per workgroup of CF::kT threads; the auction's rounds run on one
-// of its waves.  WPE waves per SIMD bound the registers: a batch that fills
-// the chip needs all its problems resident at once, a smaller one is better
-// served without the register cap.
+// LDS of the auction alone.
+template <class CF>
+__host__ __device__ inline LdsState<CF> carve_auction(char* base, int32_t R, int32_t K) {
+  LdsState<CF> w{};
+  const size_t S1 = R * K > 0 ? (size_t)R * K : 1, R_ = (size_t)R;
+  constexpr size_t TW = CF::kTW, SC = CF::kSC, DC = CF::kDC;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* q = base + off;
+    off = (off + bytes + 15) & ~(size_t)15;
+    return q;
+  };
+  w.slot_ec = (int16_t*)take(2 * S1);  // next slots of the bid groups
+  w.amt = (int32_t*)take(4 * S1);
+  w.work = (int32_t*)take(4 * S1); w.sstate = (uint16_t*)take(2 * S1);
+  w.price = (double*)take(8 * R_); w.rkey = (uint32_t*)take(4 * R_); w.cnt = (int32_t*)take(4 * R_);
+  w.vmask = (uint64_t*)take(8 * DC * TW); w.vwords = (uint32_t*)take(TW > 4 ? 4 * DC : 0);
+  w.dexp = (int32_t*)take(4 * DC);
+  w.planes = (uint64_t*)take(8 * CF::kPL * TW);
+  w.lvl = (uint64_t*)take(2 * 8 * TW); w.rel = (uint64_t*)take(8 * kRelPlanes * TW);
+  w.cn = (int8_t*)take(SC);
+  w.cv = (double*)take(8 * SC * kTierMax); w.cvr = (int32_t*)take(4 * SC * kTierMax);
+  w.cw = (uint32_t*)take(4 * SC * kTierMax);
+  w.cm = (uint64_t*)take(8 * SC * kTierMax * TW);
+  w.bytes = off;
+  return w;
+}
+
+// The auction's start by NT threads: no services, and the tables of the bonus
+// tiers.
+template <class CF, int NT>
+__device__ __forceinline__ void auction_start(const LdsState<CF>& L, const LdsParams& wp, int32_t R) {
+  constexpr int TW = CF::kTW;
+  const int tid = threadIdx.x;
+  for (int32_t r = tid; r < R; r += NT) {
+    L.price[r] = 0.0;
+    L.rkey[r] = 0;
+    L.cnt[r] = 0;
+  }
+  for (int32_t q = tid; q < CF::kPL * TW; q += NT) L.planes[q] = 0ull;
+  // every rank starts with 0 services: at the base count 0, code 0
+  for (int32_t q = tid; q < TW; q += NT) {
+    const int32_t lo = q * kWave;
+    L.lvl[q] = lo >= R ? 0ull : (R - lo >= kWave ? ~0ull : (1ull << (R - lo)) - 1ull);
+    L.lvl[TW + q] = 0ull;
+  }
+  for (int32_t q = tid; q < kRelPlanes * TW; q += NT) L.rel[q] = 0ull;
+  const int32_t ns = wp.hdr[0];
+  for (int32_t q = tid; q < ns; q += NT) L.cn[q] = (int8_t)wp.cn[q];
+  for (int32_t q = tid; q < ns * kTierMax; q += NT) {
+    L.cv[q] = wp.cv[q];
+    L.cvr[q] = wp.cvr[q];
+    L.cw[q] = wp.cw[q];
+  }
+  for (int32_t q = tid; q < ns * kTierMax * TW; q += NT) {
+    const int32_t e = q / TW;
+    L.cm[e * TW + set_word<TW>(e / kTierMax, q % TW)] = wp.cm[q];
+  }
+}
+
+// Rounds and results of problem b on one wave.
+template <class CF>
+__device__ __forceinline__ void auction_problem(const LdsState<CF>& L, const LdsParams& wp, int64_t b, int32_t nw,
+                                                int32_t used2) {
+  const SchParams& p = wp.s;
+  const int32_t R = p.R, S = p.R * p.K;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t tmax = p.t_max > 0 ? p.t_max : (int64_t)S * (R + 1);
+  const int64_t rounds = auction_rounds<CF>(L, L.slot_ec, wp.nprime + b * (int64_t)CF::kDC * R,
+                                            p.X + b * (int64_t)R * S, R, S, nw, p.price_step, tmax);
+  int64_t left = 0;  // (a slot without an expert plans 0 tokens)
+  for (int32_t s = lane; s < S; s += kWave) left += L.amt[s];
+  const int64_t tot = wave_sum_i64(left);
+  if (lane == 0) {
+    p.unfilled[b] = tot;
+    if (p.rounds_used) { p.rounds_used[2 * b] = used2; p.rounds_used[2 * b + 1] = (int32_t)rounds; }
+    if (p.status) p.status[b] = tot > 0 ? TAOT_ST_UNFILLED : 0u;
+    wp.fallback[b] = 0;
+  }
+}
+
+// The auction of one problem per one-wave workgroup, for the configurations
+// whose matching kernel has several waves: it needs few waves but many
+// registers, and other workgroups' matching can take the compute unit's rest.
+template <class CF>
+__global__ void __launch_bounds__(kWave) auction_kernel(LdsParams wp) {
+  constexpr int TW = CF::kTW;
+  extern __shared__ __attribute__((aligned(16))) char lds_dyn[];
+  const int64_t b = blockIdx.x;
+  const int4 h = wp.h.hdr[b];
+  if (h.x < 0) return;
+  const int lane = threadIdx.x;
+  const int32_t R = wp.s.R, S = wp.s.R * wp.s.K;
+  const LdsState<CF> L = carve_auction<CF>(lds_dyn, R, wp.s.K);
+  auction_start<CF, kWave>(L, wp, R);
+  for (int32_t q = lane; q < S; q += kWave) {
+    L.amt[q] = wp.h.amt[b * S + q];
+    L.slot_ec[q] = wp.h.gnext[b * S + q];
+    L.sstate[q] = 0;  // no bid yet
+  }
+  for (int32_t q = lane; q < h.x; q += kWave) L.work[q] = wp.h.work[b * S + q];
+  for (int32_t q = lane; q < h.z; q += kWave) {
+    L.dexp[q] = wp.h.nmax[b * CF::kDC + q];
+    if constexpr (TW > 4) L.vwords[q] = wp.h.vwords[b * CF::kDC + q];
+  }
+  for (int32_t q = lane; q < h.z * TW; q += kWave) L.vmask[q] = wp.h.vmask[b * CF::kDC * TW + q];
+  __syncthreads();
+  auction_problem<CF>(L, wp, b, __builtin_amdgcn_readfirstlane(h.x), h.y);
+}
+
+// Validation, matching and the auction's lists of one problem per workgroup of
+// CF::kT threads; a one-wave workgroup runs the auction too.  WPE waves per SIMD
+// bound the registers: a batch that fills the chip needs all its problems
+// resident at once, a smaller one is better served without the register cap.
 template <class CF, int WPE>
 __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp) {
   constexpr int NT = CF::kT, NW = NT / kWave, TW = CF::kTW;
   extern __shared__ __attribute__((aligned(16))) char lds_dyn[];
   __shared__ int32_t wave_cnt[NW];
   __shared__ int32_t flagbuf[2 * NW];
-  __shared__ int32_t sh_nw, simd_of[NW];
+  __shared__ int32_t sh_nw;
   __shared__ unsigned long long sh_sum, sh_big;
   const SchParams& p = wp.s;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
@@ -1404,7 +1599,10 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
   LdsState<CF> L = carve_lds<CF>(lds_dyn, R, K, wp.NEC);
 
   if (wp.hdr[1] == 0) {  // the LDS-resident auction would not be exact for this Bauct and step
-    if (tid == 0) wp.fallback[b] = 1;
+    if (tid == 0) {
+      wp.fallback[b] = 1;
+      if constexpr (NW > 1) wp.h.hdr[b] = int4{-1, 0, 0, 0};
+    }
     return;
   }
   const int64_t* spill = p.spill + b * E;
@@ -1432,6 +1630,7 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
       if (p.rounds_used) { p.rounds_used[2 * b] = 0; p.rounds_used[2 * b + 1] = 0; }
       if (p.status) p.status[b] = TAOT_ST_BAD_INPUT;
       wp.fallback[b] = 0;
+      if constexpr (NW > 1) wp.h.hdr[b] = int4{-1, 0, 0, 0};
     }
     return;
   }
@@ -1473,7 +1672,10 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
   }
   __syncthreads();
   if (ne > wp.NEC || sh_sum > (unsigned long long)INT_MAX || sh_big > (unsigned long long)INT_MAX) {
-    if (tid == 0) wp.fallback[b] = 1;
+    if (tid == 0) {
+      wp.fallback[b] = 1;
+      if constexpr (NW > 1) wp.h.hdr[b] = int4{-1, 0, 0, 0};
+    }
     return;
   }
   for (int32_t q = tid; q < nc * K; q += NT) L.assigned[q] = -1;
@@ -1604,7 +1806,10 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
     D += tot;
   }
   if (D > CF::kDC) {
-    if (tid == 0) wp.fallback[b] = 1;
+    if (tid == 0) {
+      wp.fallback[b] = 1;
+      if constexpr (NW > 1) wp.h.hdr[b] = int4{-1, 0, 0, 0};
+    }
     return;
   }
   __syncthreads();
@@ -1634,7 +1839,7 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
         const int32_t most = wave_max_i32(v[u]);
         if (lane == 0) {
           atomicMax(&L.work[d], most);
-          L.vmask[d * TW + wid] = m;
+          L.vmask[d * TW + set_word<TW>(d, wid)] = m;
           if constexpr (TW > 4)
             if (m) atomicOr(&L.vwords[d], 1u << wid);
         }
@@ -1713,28 +1918,6 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
   __syncthreads();  // every item is read before the list overwrites the array
 #pragma unroll
   for (int i = 0; i < kSlotsPerThread; ++i) list_append(mine[i] >= 0, mine[i], L.work, &sh_nw);
-  for (int32_t s = tid; s < S; s += NT) L.sstate[s] = 0;  // no bid yet
-  for (int32_t r = tid; r < R; r += NT) {
-    L.price[r] = 0.0;
-    L.rkey[r] = 0;
-    L.cnt[r] = 0;
-  }
-  for (int32_t q = tid; q < CF::kPL * TW; q += NT) L.planes[q] = 0ull;
-  // every rank starts with 0 services: at the base count 0, code 0
-  for (int32_t q = tid; q < TW; q += NT) {
-    const int32_t lo = q * kWave;
-    L.lvl[q] = lo >= R ? 0ull : (R - lo >= kWave ? ~0ull : (1ull << (R - lo)) - 1ull);
-    L.lvl[TW + q] = 0ull;
-  }
-  for (int32_t q = tid; q < kRelPlanes * TW; q += NT) L.rel[q] = 0ull;
-  const int32_t ns = wp.hdr[0];
-  for (int32_t q = tid; q < ns; q += NT) L.cn[q] = (int8_t)wp.cn[q];
-  for (int32_t q = tid; q < ns * kTierMax; q += NT) {
-    L.cv[q] = wp.cv[q];
-    L.cvr[q] = wp.cvr[q];
-    L.cw[q] = wp.cw[q];
-  }
-  for (int32_t q = tid; q < ns * kTierMax * TW; q += NT) L.cm[q] = wp.cm[q];
   // X starts at zero; every (rank, slot) pair is served at most once (after a
   // transfer either the rank holds no more tokens of the slot's expert or the
   // slot is full), so transfers below are plain stores
@@ -1748,30 +1931,24 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
       for (int64_t q = tid; q < (int64_t)R * S; q += NT) Xb[q] = 0;
     }
   }
-  // HW_ID bits 5:4 hold the SIMD of the wave
-  if (NW > 1 && lane == 0) simd_of[wid] = (int32_t)__builtin_amdgcn_s_getreg((1 << 11) | (4 << 6) | 4);
   __syncthreads();
-  if constexpr (NW > 1) {
-    // one wave goes on: on another SIMD in each of the workgroups that follow
-    // one another on a compute unit (any choice gives the same schedule)
-    const int want = (int)(blockIdx.x >> 8) & 3;
-    int it = 0;
-    for (int w = NW - 1; w >= 0; --w) it = simd_of[w] == want ? w : it;
-    if (__builtin_amdgcn_readfirstlane(wid) != it) return;
-  }
-  const int64_t tmax = p.t_max > 0 ? p.t_max : (int64_t)S * (R + 1);
-  const int64_t rounds = auction_rounds<CF>(L, gnext, np, Xb, R, S, sh_nw, p.price_step, tmax);
-
-  int64_t left = 0;
-  // (a slot without an expert plans 0 tokens; the slot experts may hold the
-  // bid groups' links by now)
-  for (int32_t s = lane; s < S; s += kWave) left += L.amt[s];
-  const int64_t tot = wave_sum_i64(left);
-  if (lane == 0) {
-    p.unfilled[b] = tot;
-    if (p.rounds_used) { p.rounds_used[2 * b] = used2; p.rounds_used[2 * b + 1] = (int32_t)rounds; }
-    if (p.status) p.status[b] = tot > 0 ? TAOT_ST_UNFILLED : 0u;
-    wp.fallback[b] = 0;
+  if constexpr (NW == 1) {
+    for (int32_t s = tid; s < S; s += NT) L.sstate[s] = 0;  // no bid yet
+    auction_start<CF, NT>(L, wp, R);
+    __syncthreads();
+    auction_problem<CF>(L, wp, b, sh_nw, used2);
+  } else {
+    for (int32_t q = tid; q < S; q += NT) {
+      wp.h.amt[b * S + q] = L.amt[q];
+      wp.h.gnext[b * S + q] = gnext[q];
+      if (q < sh_nw) wp.h.work[b * S + q] = L.work[q];
+    }
+    for (int32_t q = tid; q < D; q += NT) {
+      wp.h.nmax[b * CF::kDC + q] = L.dexp[q];
+      if constexpr (TW > 4) wp.h.vwords[b * CF::kDC + q] = L.vwords[q];
+    }
+    for (int32_t q = tid; q < D * TW; q += NT) wp.h.vmask[b * CF::kDC * TW + q] = L.vmask[q];
+    if (tid == 0) wp.h.hdr[b] = int4{sh_nw, used2, D, 0};
   }
 }
 }  // namespace
@@ -1794,6 +1971,7 @@ struct SchWs {
   uint64_t* cm;        // [SC][kTierMax][TW]
   int32_t* hdr;        // [2]
   int32_t* nprime;     // [B][DC][R]
+  Handoff h;
   int64_t slab_bytes;
   size_t bytes;
 };
@@ -1818,6 +1996,14 @@ SchWs carve_sched(void* ws, int32_t B, int32_t R, int32_t E, int32_t K) {
   w.cm = c.take<uint64_t>(SC * kTierMax * TW);
   w.hdr = c.take<int32_t>(2);
   w.nprime = c.take<int32_t>((size_t)B * DC * R);
+  const size_t HB = lds_path ? (size_t)B : 0, S = (size_t)R * K;
+  w.h.hdr = c.take<int4>(HB);
+  w.h.amt = c.take<int32_t>(HB * S);
+  w.h.work = c.take<int32_t>(HB * S);
+  w.h.gnext = c.take<int16_t>(HB * S);
+  w.h.nmax = c.take<int32_t>(HB * DC);
+  w.h.vwords = c.take<uint32_t>(HB * DC);
+  w.h.vmask = c.take<uint64_t>(HB * DC * TW);
   w.bytes = c.off;
   return w;
 }
@@ -1853,8 +2039,9 @@ taot_status launch_lds_path(const SchParams& p, const SchWs& w, int32_t B, int32
   launched = false;
   const int32_t NEC = E < CF::kNEC ? E : CF::kNEC;  // candidate experts (spill > 0) held in LDS
   const int64_t S = (int64_t)R * K;
-  const size_t slds = carve_lds<CF>(nullptr, R, K, NEC).bytes;
-  if (R > CF::kTW * kWave || S <= 0 || S > CF::kMaxS || slds > max_lds_per_block()) return TAOT_OK;
+  const size_t slds = carve_lds<CF>(nullptr, R, K, NEC).bytes, alds = carve_auction<CF>(nullptr, R, K).bytes;
+  if (R > CF::kTW * kWave || S <= 0 || S > CF::kMaxS || slds > max_lds_per_block() || alds > max_lds_per_block())
+    return TAOT_OK;
   hipLaunchKernelGGL(auction_tiers_kernel<CF::kTW>, dim3((unsigned)R), dim3(256), 0, stream, p.Bauct, R, w.ntier,
                      w.tv, w.tmask);
   if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
@@ -1865,14 +2052,22 @@ taot_status launch_lds_path(const SchParams& p, const SchWs& w, int32_t B, int32
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     return TAOT_ERR_LAUNCH;
-  const LdsParams wp{p, w.sidx, w.cn, w.cv, w.cvr, w.cw, w.cm, w.hdr, w.fallback, w.nprime, NEC};
+  const LdsParams wp{p, w.h, w.sidx, w.cn, w.cv, w.cvr, w.cw, w.cm, w.hdr, w.fallback, w.nprime, NEC};
   taot_status st;
   // a batch of more problems than fit six to a compute unit takes the
   // register-capped build, which can hold CF::kWavesPerEU per SIMD
   const bool cap = (int64_t)B > (int64_t)6 * cus;
   st = cap ? launch_lds_kernel<CF, CF::kWavesPerEU>(wp, B, slds, stream) : launch_lds_kernel<CF, 1>(wp, B, slds, stream);
-  launched = st == TAOT_OK;
-  return st;
+  if (st != TAOT_OK) return st;
+  if constexpr (CF::kT > kWave) {
+    if (alds > 65536 && hipFuncSetAttribute((const void*)auction_kernel<CF>,
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)alds) != hipSuccess)
+      return TAOT_ERR_LAUNCH;
+    hipLaunchKernelGGL(auction_kernel<CF>, dim3((unsigned)B), dim3(kWave), alds, stream, wp);
+    if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
+  }
+  launched = true;
+  return TAOT_OK;
 }
 
 }  // namespace
