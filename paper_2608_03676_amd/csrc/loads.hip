@@ -33,7 +33,11 @@ constexpr int kCsrThreads = 1024;
 constexpr int kHistThreads = 256;
 constexpr int kHistUnroll = 4;
 constexpr int kMargThreads = 256;
+constexpr int kMargManyThreads = 1024;         // (B, R, E) = (1, 1024, 4096): 106 us a call, 121 with 256 threads
+constexpr int32_t kMargFewItems = 1024;        // (16, 64, 256): 20.6 us a call with 1024 threads, 17.9 with 256
+constexpr int32_t kMargStageExperts = 4096;    // 12 bytes each, and the ranks', within 64 KiB of LDS
 constexpr int kColThreads = 256;
+constexpr unsigned kDeepBlocks = 256;          // up to one block per compute unit: 1024 threads each
 constexpr int kColExperts = 4 * kWave;         // experts per expert_load_kernel block
 constexpr int kHistLdsWords = 16384;           // 64 KiB of 32-bit counters per block when possible
 constexpr int kHistLdsWords16 = 8200;          // about 32 KiB of 16-bit counter pairs
@@ -112,7 +116,9 @@ home_csr_kernel(const int32_t* __restrict__ home, int32_t B, int32_t R, int32_t 
 // row goes in batches of kHistUnroll 16-byte loads per thread, none of them
 // predicated, with the next batch in flight while the current one is counted
 // (two register sets, a and b, take turns).  The first batch is issued before
-// the counters are cleared.
+// the counters are cleared.  A row may start and end off a 16-byte boundary
+// (N % 4 != 0): the ids before the first and behind the last go one by one (7 x
+// 24 rows of 73734 ids: 25 us a call; 92 when such rows were read id by id).
 template <bool PACK16>
 __global__ void __launch_bounds__(kHistThreads)
 histogram_kernel(const int32_t* __restrict__ ids, int64_t N, int32_t R, int32_t E, int32_t copies, bool half,
@@ -135,10 +141,12 @@ histogram_kernel(const int32_t* __restrict__ ids, int64_t N, int32_t R, int32_t 
     count(v.z);
     count(v.w);
   };
-  const bool vec = (N % 4 == 0) && ((reinterpret_cast<uintptr_t>(src) & 15u) == 0);
-  const v4i* s4 = reinterpret_cast<const v4i*>(src);
+  // up to three ids before the first 16-byte boundary, and up to three behind the last
+  const int64_t lead = (int64_t)((0u - (uint32_t)(reinterpret_cast<uintptr_t>(src) >> 2)) & 3u);
+  const int64_t head = lead < N ? lead : N, n4 = (N - head) / 4, tail = head + 4 * n4;
+  const v4i* s4 = reinterpret_cast<const v4i*>(src + head);
   constexpr int64_t kStep = (int64_t)kHistThreads * kHistUnroll;
-  const int64_t nb = vec ? (N / 4) / kStep : 0;  // full batches
+  const int64_t nb = n4 / kStep;  // full batches
   const v4i* p = s4 + threadIdx.x;
   v4i a[kHistUnroll], b[kHistUnroll];
   if (nb > 0) {
@@ -173,14 +181,17 @@ histogram_kernel(const int32_t* __restrict__ ids, int64_t N, int32_t R, int32_t 
       ++m;
     }
   }
-  // what the full batches left: the vector tail, or the whole row when it is
-  // not 16-byte aligned
-  if (vec) {
-    for (int64_t i = nb * kStep + threadIdx.x; i < N / 4; i += kHistThreads)
-      count4(__builtin_nontemporal_load(&s4[i]));
-  } else {
-    for (int64_t i = threadIdx.x; i < N; i += kHistThreads) count(src[i]);
-  }
+  // what the full batches left: less than one batch, and the ids off the
+  // 16-byte boundaries
+  const int64_t rest = nb * kStep + threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < kHistUnroll; ++u)
+    if (rest + u * kHistThreads < n4) a[u] = __builtin_nontemporal_load(s4 + rest + u * kHistThreads);
+  if ((int64_t)threadIdx.x < head) count(src[threadIdx.x]);
+  if ((int64_t)threadIdx.x < N - tail) count(src[tail + threadIdx.x]);
+#pragma unroll
+  for (int u = 0; u < kHistUnroll; ++u)
+    if (rest + u * kHistThreads < n4) count4(a[u]);
   __syncthreads();
   // The counts are not read again by this kernel, and ordinary stores of them
   // interleaved with the id stream cost far more read bandwidth than their
@@ -243,10 +254,13 @@ histogram_kernel(const int32_t* __restrict__ ids, int64_t N, int32_t R, int32_t 
 // whole block of a row, and its stores use the values of all its loads, so
 // every word of the row is read before any is overwritten; other waves and
 // blocks touch other rows or other blocks.
-template <bool HALF>
-__global__ void __launch_bounds__(kColThreads)
+//
+// Few blocks (a small batch) leave most of the chip idle and the time is the
+// waves' chain of row loads: NT = 1024 then cuts it to a quarter.
+template <bool HALF, int NT>
+__global__ void __launch_bounds__(NT)
 expert_load_kernel(int32_t* __restrict__ n, int32_t R, int32_t E, int64_t* __restrict__ load_e) {
-  constexpr int kWaves = kColThreads / kWave;
+  constexpr int kWaves = NT / kWave;
   constexpr int kRowsInFlight = 8;
   __shared__ long long part[kWaves][kColExperts];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
@@ -315,9 +329,10 @@ struct HotCold {
   int32_t* cold_cnt;
 };
 
-// Exclusive positions of two flags among the kMargThreads threads (ascending
+// Exclusive positions of two flags among the NT threads (ascending
 // thread id) and their totals.  All threads must call it.
-__device__ __forceinline__ void block_scan2(bool f0, bool f1, int32_t (*cnt)[kMargThreads / kWave], int32_t& p0,
+template <int NT>
+__device__ __forceinline__ void block_scan2(bool f0, bool f1, int32_t (*cnt)[NT / kWave], int32_t& p0,
                                             int32_t& p1, int32_t& t0, int32_t& t1) {
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
   const uint64_t m0 = __ballot(f0), m1 = __ballot(f1);
@@ -328,7 +343,7 @@ __device__ __forceinline__ void block_scan2(bool f0, bool f1, int32_t (*cnt)[kMa
   }
   __syncthreads();
   int32_t o0 = 0, o1 = 0, s0 = 0, s1 = 0;
-  for (int w = 0; w < kMargThreads / kWave; ++w) {
+  for (int w = 0; w < NT / kWave; ++w) {
     const int32_t a = cnt[0][w], c = cnt[1][w];
     o0 += w < wid ? a : 0;
     o1 += w < wid ? c : 0;
@@ -342,8 +357,14 @@ __device__ __forceinline__ void block_scan2(bool f0, bool f1, int32_t (*cnt)[kMa
   t1 = s1;
 }
 
-// One block per problem; x_e comes from expert_load_kernel.
-__global__ void __launch_bounds__(kMargThreads)
+// One block per problem; x_e comes from expert_load_kernel.  What bounds it is
+// the chain of dependent loads per thread (list position -> expert -> load),
+// so with STAGE the lists' experts and loads go to LDS once, side by side in
+// list order, and with many ranks and experts the block has four times the
+// threads.  One call for (B, R, E) = (1, 1024, 4096) with 65536 ids a row:
+// 214 us before this and the deep expert_load_kernel, 106 with both.
+template <int NT, bool STAGE>
+__global__ void __launch_bounds__(NT)
 marginals_kernel(int32_t R, int32_t E, const int32_t* __restrict__ home, const int32_t* __restrict__ rank_ptr,
                  const int32_t* __restrict__ rank_exp, const int32_t* __restrict__ bad_home,
                  const unsigned long long* __restrict__ bad_prob, int64_t* __restrict__ load_e,
@@ -353,21 +374,21 @@ marginals_kernel(int32_t R, int32_t E, const int32_t* __restrict__ home, const i
                  HotCold hc, uint32_t* __restrict__ status) {
   const int64_t b = blockIdx.x;
   const int tid = threadIdx.x;
-  __shared__ int64_t red_s[kMargThreads / kWave], red_m[kMargThreads / kWave];
-  __shared__ int32_t scan_cnt[2][kMargThreads / kWave];
+  __shared__ int64_t red_s[NT / kWave], red_m[NT / kWave];
+  __shared__ int32_t scan_cnt[2][NT / kWave];
   __shared__ int64_t sh_L, sh_max;
   const bool home_bad = bad_home[0] != 0;
   const int64_t skipped = (int64_t)bad_prob[b];  // ids of this problem outside [0, E)
 
   int64_t* xe = load_e + b * E;
   if (home_bad) {
-    for (int32_t e = tid; e < E; e += kMargThreads) { xe[e] = 0; spill[b * E + e] = 0; }
-    for (int32_t r = tid; r < R; r += kMargThreads) {
+    for (int32_t e = tid; e < E; e += NT) { xe[e] = 0; spill[b * E + e] = 0; }
+    for (int32_t r = tid; r < R; r += NT) {
       load_r[b * R + r] = 0; excess[b * R + r] = 0; spare[b * R + r] = 0;
       if (supply) supply[b * R + r] = 0.f;
       if (demand) demand[b * R + r] = 0.f;
     }
-    for (int32_t r = tid; r < R; r += kMargThreads) {
+    for (int32_t r = tid; r < R; r += NT) {
       if (hc.hot_idx) hc.hot_idx[b * R + r] = -1;
       if (hc.cold_idx) hc.cold_idx[b * R + r] = -1;
     }
@@ -382,11 +403,28 @@ marginals_kernel(int32_t R, int32_t E, const int32_t* __restrict__ home, const i
     return;
   }
 
+  extern __shared__ __attribute__((aligned(16))) char stage[];
+  int64_t* const lx = reinterpret_cast<int64_t*>(stage);       // [E] load of the expert at a list position
+  int32_t* const le = reinterpret_cast<int32_t*>(lx + E);      // [E] the expert
+  int32_t* const lp = le + E;                                  // [R + 1] rank_ptr
+  if constexpr (STAGE) {
+    for (int32_t q = tid; q < E; q += NT) {
+      const int32_t e = rank_exp[q];
+      le[q] = e;
+      lx[q] = xe[e];
+    }
+    for (int32_t r = tid; r <= R; r += NT) lp[r] = rank_ptr[r];
+    __syncthreads();
+  }
+  auto ptr_at = [&](int32_t r) { return STAGE ? lp[r] : rank_ptr[r]; };
+  auto exp_at = [&](int32_t q) { return STAGE ? le[q] : rank_exp[q]; };
+  auto load_at = [&](int32_t q) { return STAGE ? lx[q] : xe[rank_exp[q]]; };
+
   // rank loads, total and maximum
   int64_t ls = 0, lm = 0;
-  for (int32_t r = tid; r < R; r += kMargThreads) {
+  for (int32_t r = tid; r < R; r += NT) {
     int64_t s = 0;
-    for (int32_t q = rank_ptr[r]; q < rank_ptr[r + 1]; ++q) s += xe[rank_exp[q]];
+    for (int32_t q = ptr_at(r), end = ptr_at(r + 1); q < end; ++q) s += load_at(q);
     load_r[b * R + r] = s;
     ls += s;
     lm = s > lm ? s : lm;
@@ -397,14 +435,14 @@ marginals_kernel(int32_t R, int32_t E, const int32_t* __restrict__ home, const i
   __syncthreads();
   if (tid == 0) {
     int64_t s = 0, m = 0;
-    for (int i = 0; i < kMargThreads / kWave; ++i) { s += red_s[i]; m = red_m[i] > m ? red_m[i] : m; }
+    for (int i = 0; i < NT / kWave; ++i) { s += red_s[i]; m = red_m[i] > m ? red_m[i] : m; }
     sh_L = s;
     sh_max = m;
   }
   __syncthreads();
   const int64_t L = sh_L;
   const int64_t mean = L / R;  // integer mean floor(L / R)
-  for (int32_t r = tid; r < R; r += kMargThreads) {
+  for (int32_t r = tid; r < R; r += NT) {
     const int64_t l = load_r[b * R + r];
     const int64_t ex = l > mean ? l - mean : 0;
     const int64_t sp = mean > l ? mean - l : 0;
@@ -418,17 +456,17 @@ marginals_kernel(int32_t R, int32_t E, const int32_t* __restrict__ home, const i
   // wrote above: same rank stride)
   if (hc.hot_idx || hc.cold_idx || hc.hot_cnt || hc.cold_cnt) {
     int32_t nh = 0, nc = 0;
-    for (int32_t base = 0; base < R; base += kMargThreads) {
+    for (int32_t base = 0; base < R; base += NT) {
       const int32_t r = base + tid;
       const int64_t l = r < R ? load_r[b * R + r] : mean;
       int32_t ph, pc, th, tc;
-      block_scan2(l > mean, l < mean, scan_cnt, ph, pc, th, tc);
+      block_scan2<NT>(l > mean, l < mean, scan_cnt, ph, pc, th, tc);
       if (l > mean && hc.hot_idx) hc.hot_idx[b * R + nh + ph] = r;
       if (l < mean && hc.cold_idx) hc.cold_idx[b * R + nc + pc] = r;
       nh += th;
       nc += tc;
     }
-    for (int32_t r = tid; r < R; r += kMargThreads) {
+    for (int32_t r = tid; r < R; r += NT) {
       if (hc.hot_idx && r >= nh) hc.hot_idx[b * R + r] = -1;
       if (hc.cold_idx && r >= nc) hc.cold_idx[b * R + r] = -1;
     }
@@ -445,13 +483,13 @@ marginals_kernel(int32_t R, int32_t E, const int32_t* __restrict__ home, const i
   }
   // spill: prefix of the expert's rank in ascending (x, id) order, then
   // sigma_k - sigma_{k-1} with sigma = max(prefix - mean, 0)
-  for (int32_t e = tid; e < E; e += kMargThreads) {
+  for (int32_t e = tid; e < E; e += NT) {
     const int32_t h = home[e];
     const int64_t x = xe[e];
     int64_t P = 0;
-    for (int32_t q = rank_ptr[h]; q < rank_ptr[h + 1]; ++q) {
-      const int32_t e2 = rank_exp[q];
-      const int64_t x2 = xe[e2];
+    for (int32_t q = ptr_at(h), end = ptr_at(h + 1); q < end; ++q) {
+      const int32_t e2 = exp_at(q);
+      const int64_t x2 = load_at(q);
       if (x2 < x || (x2 == x && e2 <= e)) P += x2;
     }
     const int64_t hi = P > mean ? P - mean : 0;
@@ -523,38 +561,41 @@ taot_status launch_plan_loads(const int32_t* ids, int32_t B, int32_t R, int64_t 
   if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   // counter layout: 32-bit copies of E+1 words while 16 fit the LDS cap;
   // else 16-bit pairs, twice as many copies in half the words, when no copy
-  // can count past 65535 (a copy's lane group reads at most N / copies ids
-  // plus one 16-byte batch tail per thread)
+  // can count past 65535 (a copy's lane group reads at most N / copies ids,
+  // one batch more per thread and the few ids off the 16-byte boundaries)
   int32_t copies = 16;
   while (copies > 1 && (int64_t)copies * (E + 1) > kHistLdsWords) copies >>= 1;
   int32_t copies16 = 16;
   const int64_t stride16 = (E >> 1) + 1;
   while (copies16 > 1 && (int64_t)copies16 * stride16 > kHistLdsWords16) copies16 >>= 1;
   const bool pack16 = copies < kHist16MinCopies && copies16 > copies &&
-                      N / copies16 + 4 * kHistUnroll * (kHistThreads / copies16) * 4 <= 65535;
+                      N / copies16 + 4 * kHistUnroll * (kHistThreads / copies16) * 4 + 8 <= 65535;
   if (pack16) copies = copies16;
   const size_t lds = (size_t)copies * (pack16 ? stride16 : (E + 1)) * sizeof(int32_t);
-  const void* hist = pack16 ? (const void*)histogram_kernel<true> : (const void*)histogram_kernel<false>;
-  if (lds > 65536 &&
-      hipFuncSetAttribute(hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+  auto* hist = pack16 ? histogram_kernel<true> : histogram_kernel<false>;
+  if (lds > 65536 && hipFuncSetAttribute((const void*)hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+                         hipSuccess)
     return TAOT_ERR_LAUNCH;
   // counts stored as 16-bit pairs (half the bytes next to the id stream) when
   // the rows are 16-byte aligned and shorter than 2 * 65535 ids
   const bool half = E % 4 == 0 && (reinterpret_cast<uintptr_t>(n) & 15u) == 0 && N < 2 * 65535;
-  if (pack16)
-    hipLaunchKernelGGL(histogram_kernel<true>, dim3((unsigned)((int64_t)B * R)), dim3(kHistThreads), lds, stream,
-                       ids, N, R, E, copies, half, n, w.bad_prob);
-  else
-    hipLaunchKernelGGL(histogram_kernel<false>, dim3((unsigned)((int64_t)B * R)), dim3(kHistThreads), lds, stream,
-                       ids, N, R, E, copies, half, n, w.bad_prob);
+  hipLaunchKernelGGL(hist, dim3((unsigned)((int64_t)B * R)), dim3(kHistThreads), lds, stream, ids, N, R, E,
+                     copies, half, n, w.bad_prob);
   if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   const dim3 col_grid((unsigned)((int64_t)B * ((E + kColExperts - 1) / kColExperts)));
-  if (half)
-    hipLaunchKernelGGL(expert_load_kernel<true>, col_grid, dim3(kColThreads), 0, stream, n, R, E, load_e);
-  else
-    hipLaunchKernelGGL(expert_load_kernel<false>, col_grid, dim3(kColThreads), 0, stream, n, R, E, load_e);
+  const bool deep = col_grid.x <= kDeepBlocks && R >= 64;
+  auto* sums = half ? (deep ? expert_load_kernel<true, 1024> : expert_load_kernel<true, kColThreads>)
+                    : (deep ? expert_load_kernel<false, 1024> : expert_load_kernel<false, kColThreads>);
+  hipLaunchKernelGGL(sums, col_grid, dim3(deep ? 1024 : kColThreads), 0, stream, n, R, E, load_e);
   if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
-  hipLaunchKernelGGL(marginals_kernel, dim3((unsigned)B), dim3(kMargThreads), 0, stream, R, E, home, w.rank_ptr,
+  const bool staged = E <= kMargStageExperts;
+  const bool many = staged && R + E > kMargFewItems;
+  auto* marg = !staged ? marginals_kernel<kMargThreads, false>
+               : many  ? marginals_kernel<kMargManyThreads, true>
+                       : marginals_kernel<kMargThreads, true>;
+  const size_t marg_lds = staged ? (size_t)E * 12 + ((size_t)R + 1) * 4 : 0;
+  hipLaunchKernelGGL(marg, dim3((unsigned)B), dim3(many ? kMargManyThreads : kMargThreads), marg_lds, stream, R, E,
+                     home, w.rank_ptr,
                      w.rank_exp, w.bad_home, w.bad_prob, load_e, load_r, excess, spare, spill, supply, demand,
                      rho, alpha, bad_ids, HotCold{hot_idx, cold_idx, hot_cnt, cold_cnt}, status);
   if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;

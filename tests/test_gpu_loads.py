@@ -74,6 +74,19 @@ def test_edge_shapes_with_bad_ids(R, E, N, gpu):
     _compare(_gpu_loads(ids, home, E), O.plan_loads(ids, home, E), f"R{R} E{E} N{N}")
 
 
+# Rows that start and end off a 16-byte boundary (N % 4 != 0), with none, one
+# and two full batches, and the forms of the later kernels: few blocks over 64
+# ranks and up, marginals of few and of many items, lists past the LDS stage.
+@pytest.mark.parametrize("B,R,E,N", [(1, 3, 40, 1), (1, 3, 40, 2), (2, 5, 40, 3), (1, 5, 33, 4097), (2, 7, 64, 4099),
+                                     (1, 9, 384, 8195), (2, 64, 260, 1026), (1, 65, 1021, 515), (1, 640, 384, 130),
+                                     (1, 640, 385, 129), (1, 33, 4096, 4094), (1, 70, 4097, 4093)])
+def test_ragged_rows(B, R, E, N, gpu):
+    rng = np.random.default_rng(N * 7 + E)
+    ids = rng.integers(-1, E + 1, size=(B, R, N)).astype(np.int32)
+    home = rng.integers(0, R, size=E).astype(np.int32)
+    _compare(_gpu_loads(ids, home, E), O.plan_loads(ids, home, E), f"R{R} E{E} N{N}")
+
+
 # Rows shorter than 2 * 65535 ids keep their counts as 16-bit pairs between
 # the histogram and the expert sums, a count above 65534 in a spare word of its
 # 256-expert block.  One expert per row takes nearly the whole row here, at
