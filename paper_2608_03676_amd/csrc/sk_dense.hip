@@ -10,8 +10,8 @@
 // workspace (one R x R matrix per problem); the iterations update only the
 // scalings u, v, so their rounding stays relative.  The first row update is
 // the exact log-domain one over all R columns from G = 0 (v = 1); an
-// out-of-range scaling triggers the exact log-domain update of its row or
-// column from C, with its row or column of K~ rebuilt.
+// out-of-range scaling triggers the exact log-domain update of its row, or of
+// its block of 16 columns, from C, with that part of K~ rebuilt.
 //
 // Each iteration is two grid-wide kernels over all problems, which keeps
 // every compute unit streaming K~ from device memory:
@@ -37,6 +37,7 @@ constexpr int kDnThreads = 256;
 constexpr int kDnWaves = kDnThreads / kWave;
 constexpr int kDnRowBlock = 64;  // rows per block of the row pass
 constexpr int kDnColBlock = 16;  // columns per block of the column kernel
+constexpr int kDnFixRows = 16;   // rows in flight per thread of an exact column update
 constexpr int kDnDepth = 1;      // row tiles in flight behind the current one
 
 // Row pass, R % 4 == 0 and C 16-byte aligned: the wave-streamed kernel, 16
@@ -591,32 +592,33 @@ dense_roww_kernel(SkParams p, float kappa) {
 // One column half-step for 16 columns of a problem: the 16 thread groups add
 // a sixteenth of the row blocks' partials each (64-byte segments per group)
 // and the first 16 threads set v_j from the group sums (added in group
-// order).  A column whose v_j leaves [2^-60, 2^60] goes to a list in LDS; the
-// four waves then take the listed columns one each for the exact log-domain
-// update from C (all RPL loads of a lane in flight at once), with the column
-// of K~ rebuilt.  Sixteen columns per block spread these updates over many
-// waves when whole batches of columns leave the range together.
-template <int RPL>
+// order).  When a v_j leaves [2^-60, 2^60], all the block's columns take the
+// exact log-domain update from C, with their columns of K~ rebuilt.
+//
+// What bounds that update is its traffic: a column of C or K~ alone moves a
+// whole segment per row, the same as the block's 16 columns, whose potentials
+// drift much alike; so the block's other columns are absorbed with the first
+// that has to be, which spares them an update of their own (64 problems of R =
+// 1024, a cost matrix each, 500 iterations: 34.0 -> 30.8 ms).
 __global__ void __launch_bounds__(kDnThreads) dense_col_kernel(SkParams p, float kappa) {
   constexpr int G = kDnThreads / kDnColBlock;
-  __shared__ float ps[G][kDnColBlock];
-  __shared__ int32_t fixl[kDnColBlock];
-  __shared__ int32_t nfix;
+  __shared__ float ps[G][kDnColBlock], pt[G][kDnColBlock];
+  extern __shared__ __attribute__((aligned(16))) float fixrow[];  // [2][R]
   const int32_t R = p.R, NB = dense_blocks(R);
   const int32_t chunks = (R + kDnColBlock - 1) / kDnColBlock;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+  const int tid = threadIdx.x;
   const int grp = tid / kDnColBlock, cl = tid % kDnColBlock;
   const int64_t pb = blockIdx.x / chunks;
   const int32_t j = (int32_t)(blockIdx.x % chunks) * kDnColBlock + cl;
   if (p.stream_flag[pb] != 0) return;  // uniform per block
   const DenseState S = dense_state(p, pb);
-  const float dj = tid < kDnColBlock && j < R ? p.b[pb * R + j] : 0.f;  // in flight with the partials
+  const float dj = j < R ? p.b[pb * R + j] : 0.f;  // in flight with the partials
   float x = 0.f;
   if (j < R)
     for (int32_t t = NB * grp / G; t < NB * (grp + 1) / G; ++t) x += S.part[(int64_t)t * R + j];
   ps[grp][cl] = x;
-  if (tid == 0) nfix = 0;
   __syncthreads();
+  bool out = false;
   if (tid < kDnColBlock && j < R) {
     if (!(dj > 0.f)) {
       // no demand: no flow into this column, and its entries of K~ are zero
@@ -628,48 +630,66 @@ __global__ void __launch_bounds__(kDnThreads) dense_col_kernel(SkParams p, float
 #pragma unroll
       for (int g = 1; g < G; ++g) xs += ps[g][cl];
       const float vn = dj * frcp(xs);
-      if (in_range(vn) || (p.flags & TAOT_SK_LINEAR)) S.v[j] = vn;
-      else fixl[atomicAdd(&nfix, 1)] = j;
+      out = !in_range(vn) && !(p.flags & TAOT_SK_LINEAR);
+      S.v[j] = vn;
     }
   }
-  __syncthreads();
+  if (__syncthreads_or(out) == 0) return;
+  // F_i and F_i + log2 u_i in LDS; thread group g takes rows g, g + 16, ... with
+  // a running maximum and sum over tiles of kDnFixRows rows in flight, and the
+  // groups' results meet in group order
   const float* Cb = p.C + pb * p.C_stride;
-  for (int32_t q = wid; q < nfix; q += kDnWaves) {
-    const int32_t c = fixl[q];
-    const float dc = p.b[pb * R + c];
-    float cc[RPL], fl[RPL], xx[RPL];
+  float* const fl = fixrow;      // [R] F_i
+  float* const fu = fixrow + R;  // [R] F_i + log2 u_i (-inf where u_i = 0)
+  for (int32_t i = tid; i < R; i += kDnThreads) {
+    const float f = S.F[i], uu = S.u[i];
+    fl[i] = f;
+    fu[i] = uu > 0.f ? f + flog2(uu) : -INFINITY;
+  }
+  __syncthreads();
+  float mx = -INFINITY, s = 0.f;
+  if (dj > 0.f) {
+    for (int32_t i0 = grp; i0 < R; i0 += kDnFixRows * G) {
+      float c[kDnFixRows];
 #pragma unroll
-    for (int k = 0; k < RPL; ++k) {
-      const int32_t i = lane + kWave * k;
-      cc[k] = 0.f;
-      fl[k] = -INFINITY;
-      float uu = 0.f;
-      if (i < R) {
-        cc[k] = Cb[(int64_t)i * R + c];
-        fl[k] = S.F[i];
-        uu = S.u[i];
+      for (int k = 0; k < kDnFixRows; ++k) c[k] = i0 + k * G < R ? Cb[(int64_t)(i0 + k * G) * R + j] : 0.f;
+      float m = mx;
+#pragma unroll
+      for (int k = 0; k < kDnFixRows; ++k) {
+        c[k] = i0 + k * G < R ? fu[i0 + k * G] - c[k] * kappa : -INFINITY;
+        m = fmaxf(m, c[k]);
       }
-      xx[k] = uu > 0.f ? (fl[k] + flog2(uu)) - cc[k] * kappa : -INFINITY;
-    }
-    float mx = -INFINITY;
+      if (m == -INFINITY) continue;
+      s *= mx == -INFINITY ? 0.f : fexp2(mx - m);
 #pragma unroll
-    for (int k = 0; k < RPL; ++k) mx = fmaxf(mx, xx[k]);
-    mx = wave_max(mx);
-    float s = 0.f;
-#pragma unroll
-    for (int k = 0; k < RPL; ++k)
-      if (xx[k] != -INFINITY) s += fexp2(xx[k] - mx);
-    s = wave_sum(s);
-    const float gc = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(flog2(dc) - (mx + flog2(s)))));
-#pragma unroll
-    for (int k = 0; k < RPL; ++k) {
-      const int32_t i = lane + kWave * k;
-      if (i < R) S.K[(int64_t)i * R + c] = fl[k] != -INFINITY ? fexp2((fl[k] + gc) - cc[k] * kappa) : 0.f;
+      for (int k = 0; k < kDnFixRows; ++k) s += c[k] == -INFINITY ? 0.f : fexp2(c[k] - m);
+      mx = m;
     }
-    if (lane == 0) {
-      S.G[c] = gc;
-      S.v[c] = 1.f;
+  }
+  ps[grp][cl] = mx;
+  pt[grp][cl] = s;
+  __syncthreads();
+  if (!(dj > 0.f)) return;
+  float M = ps[0][cl];
+#pragma unroll
+  for (int g = 1; g < G; ++g) M = fmaxf(M, ps[g][cl]);
+  float sum = 0.f;
+#pragma unroll
+  for (int g = 0; g < G; ++g) sum += ps[g][cl] == -INFINITY ? 0.f : pt[g][cl] * fexp2(ps[g][cl] - M);
+  const float gc = flog2(dj) - (M + flog2(sum));
+  for (int32_t i0 = grp; i0 < R; i0 += kDnFixRows * G) {
+    float c[kDnFixRows];
+#pragma unroll
+    for (int k = 0; k < kDnFixRows; ++k) c[k] = i0 + k * G < R ? Cb[(int64_t)(i0 + k * G) * R + j] : 0.f;
+#pragma unroll
+    for (int k = 0; k < kDnFixRows; ++k) {
+      const int32_t i = i0 + k * G;
+      if (i < R) S.K[(int64_t)i * R + j] = fl[i] != -INFINITY ? fexp2((fl[i] + gc) - c[k] * kappa) : 0.f;
     }
+  }
+  if (grp == 0) {
+    S.G[j] = gc;
+    S.v[j] = 1.f;
   }
 }
 
@@ -789,14 +809,12 @@ taot_status launch_dense(const SkParams& p, hipStream_t stream) {
   const unsigned row_grid = (unsigned)((int64_t)B * dense_blocks(R));
   const unsigned col_grid = (unsigned)((int64_t)B * ((R + kDnColBlock - 1) / kDnColBlock));
   const unsigned out_grid = (unsigned)((int64_t)B * ((R + kDnThreads - 1) / kDnThreads));
+  const size_t fix_lds = (size_t)2 * R * sizeof(float);
   for (int32_t it = 1; it <= p.iters; ++it) {
     const taot_status st = it == 1 ? launch_rows<true>(p, kappa, row_grid, stream)
                                    : launch_rows<false>(p, kappa, row_grid, stream);
     if (st != TAOT_OK) return st;
-    if (R <= 16 * kWave)
-      hipLaunchKernelGGL(dense_col_kernel<16>, dim3(col_grid), dim3(kDnThreads), 0, stream, p, kappa);
-    else
-      hipLaunchKernelGGL(dense_col_kernel<32>, dim3(col_grid), dim3(kDnThreads), 0, stream, p, kappa);
+    hipLaunchKernelGGL(dense_col_kernel, dim3(col_grid), dim3(kDnThreads), fix_lds, stream, p, kappa);
   }
   if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   const bool colcap = p.T && !(p.flags & TAOT_SK_NO_COLCAP);

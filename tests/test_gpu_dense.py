@@ -75,6 +75,25 @@ def test_dense_ragged_shapes(R, per_problem, gpu):
         _check(a, b, C, eps, iters, flags)
 
 
+@pytest.mark.parametrize("R", [15, 16, 31, 257, 272, 1025])
+def test_dense_column_updates(R, gpu):
+    """Costs of 120 to 200 eps with a column's share of its own take column
+    scalings past 2^60 in different iterations: the block's 16 columns then
+    take the exact update together, with columns of no demand among them, a
+    ragged last block, and one to five tiles of rows."""
+    rng = np.random.default_rng(R)
+    a = np.zeros((2, R), np.float32)
+    b = np.zeros((2, R), np.float32)
+    hot = rng.random((2, R)) < 0.3
+    hot[:, 0], hot[:, 1] = True, False
+    a[hot] = rng.integers(1, 3000, size=int(hot.sum()))
+    cold = ~hot & (rng.random((2, R)) < 0.8)
+    cold[:, 1] = True
+    b[cold] = rng.integers(1, 3000, size=int(cold.sum()))
+    C = (rng.uniform(3.0, 4.0, size=(2, R, R)) * rng.uniform(0.8, 1.0, size=(2, 1, R))).astype(np.float32)
+    _check(a, b, C, 0.02, 40)
+
+
 def test_dense_stress_shape_per_problem_costs(gpu):
     """The workload-4 shape (R = 1024, the fat-tree costs) with one cost matrix
     per problem, fewer iterations so that the oracle stays quick."""
