@@ -37,7 +37,7 @@ constexpr int kDnThreads = 256;
 constexpr int kDnWaves = kDnThreads / kWave;
 constexpr int kDnRowBlock = 64;  // rows per block of the row pass
 constexpr int kDnColBlock = 16;  // columns per block of the column kernel
-constexpr int kDnFixRows = 16;   // rows in flight per thread of an exact column update
+constexpr int kDnFixRows = 16;   // rows in flight per thread of an exact column update (32 and 64: slower, fewer waves fit)
 constexpr int kDnDepth = 1;      // row tiles in flight behind the current one
 
 // Row pass, R % 4 == 0 and C 16-byte aligned: the wave-streamed kernel, 16
@@ -599,11 +599,11 @@ dense_roww_kernel(SkParams p, float kappa) {
 // whole segment per row, the same as the block's 16 columns, whose potentials
 // drift much alike; so the block's other columns are absorbed with the first
 // that has to be, which spares them an update of their own (64 problems of R =
-// 1024, a cost matrix each, 500 iterations: 34.0 -> 30.8 ms).
-__global__ void __launch_bounds__(kDnThreads) dense_col_kernel(SkParams p, float kappa) {
+// 1024, a cost matrix each, 500 iterations: 34.0 -> 30.4 ms).
+__global__ void __launch_bounds__(kDnThreads, 8) dense_col_kernel(SkParams p, float kappa) {
   constexpr int G = kDnThreads / kDnColBlock;
   __shared__ float ps[G][kDnColBlock], pt[G][kDnColBlock];
-  extern __shared__ __attribute__((aligned(16))) float fixrow[];  // [2][R]
+  extern __shared__ __attribute__((aligned(16))) float fixrow[];  // [2][whole tiles of rows]
   const int32_t R = p.R, NB = dense_blocks(R);
   const int32_t chunks = (R + kDnColBlock - 1) / kDnColBlock;
   const int tid = threadIdx.x;
@@ -639,30 +639,34 @@ __global__ void __launch_bounds__(kDnThreads) dense_col_kernel(SkParams p, float
   // a running maximum and sum over tiles of kDnFixRows rows in flight, and the
   // groups' results meet in group order
   const float* Cb = p.C + pb * p.C_stride;
-  float* const fl = fixrow;      // [R] F_i
-  float* const fu = fixrow + R;  // [R] F_i + log2 u_i (-inf where u_i = 0)
-  for (int32_t i = tid; i < R; i += kDnThreads) {
-    const float f = S.F[i], uu = S.u[i];
+  float* const fl = fixrow;         // [rows] F_i
+  const int32_t rows = (R + kDnFixRows * G - 1) / (kDnFixRows * G) * (kDnFixRows * G);  // whole tiles
+  float* const fu = fixrow + rows;  // [rows] F_i + log2 u_i (-inf where u_i = 0, and off the matrix)
+  for (int32_t i = tid; i < rows; i += kDnThreads) {
+    const float f = i < R ? S.F[i] : 0.f, uu = i < R ? S.u[i] : 0.f;
     fl[i] = f;
     fu[i] = uu > 0.f ? f + flog2(uu) : -INFINITY;
   }
   __syncthreads();
   float mx = -INFINITY, s = 0.f;
+  float c[kDnFixRows];  // the tile's entries of C
+  const uint32_t at0 = (uint32_t)j;
+  auto load_tile = [&](int32_t i0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < kDnFixRows; ++k) c[k] = Cb[at0 + (uint32_t)(min(i0 + k * G, R - 1) * R)];
+  };
   if (dj > 0.f) {
     for (int32_t i0 = grp; i0 < R; i0 += kDnFixRows * G) {
-      float c[kDnFixRows];
-#pragma unroll
-      for (int k = 0; k < kDnFixRows; ++k) c[k] = i0 + k * G < R ? Cb[(int64_t)(i0 + k * G) * R + j] : 0.f;
+      load_tile(i0);
+      auto at = [&](int k) { return fu[i0 + k * G] - c[k] * kappa; };
       float m = mx;
 #pragma unroll
-      for (int k = 0; k < kDnFixRows; ++k) {
-        c[k] = i0 + k * G < R ? fu[i0 + k * G] - c[k] * kappa : -INFINITY;
-        m = fmaxf(m, c[k]);
-      }
+      for (int k = 0; k < kDnFixRows; ++k) m = fmaxf(m, at(k));
       if (m == -INFINITY) continue;
+      asm volatile("" ::: "memory");  // fu is read again: a tile of it would take as many registers as c
       s *= mx == -INFINITY ? 0.f : fexp2(mx - m);
 #pragma unroll
-      for (int k = 0; k < kDnFixRows; ++k) s += c[k] == -INFINITY ? 0.f : fexp2(c[k] - m);
+      for (int k = 0; k < kDnFixRows; ++k) s += fexp2(at(k) - m);
       mx = m;
     }
   }
@@ -677,14 +681,13 @@ __global__ void __launch_bounds__(kDnThreads) dense_col_kernel(SkParams p, float
 #pragma unroll
   for (int g = 0; g < G; ++g) sum += ps[g][cl] == -INFINITY ? 0.f : pt[g][cl] * fexp2(ps[g][cl] - M);
   const float gc = flog2(dj) - (M + flog2(sum));
+  const bool kept = R <= kDnFixRows * G;  // one tile: its entries are still there
   for (int32_t i0 = grp; i0 < R; i0 += kDnFixRows * G) {
-    float c[kDnFixRows];
-#pragma unroll
-    for (int k = 0; k < kDnFixRows; ++k) c[k] = i0 + k * G < R ? Cb[(int64_t)(i0 + k * G) * R + j] : 0.f;
+    if (!kept) load_tile(i0);
 #pragma unroll
     for (int k = 0; k < kDnFixRows; ++k) {
       const int32_t i = i0 + k * G;
-      if (i < R) S.K[(int64_t)i * R + j] = fl[i] != -INFINITY ? fexp2((fl[i] + gc) - c[k] * kappa) : 0.f;
+      if (i < R) S.K[at0 + (uint32_t)(i * R)] = fl[i] != -INFINITY ? fexp2((fl[i] + gc) - c[k] * kappa) : 0.f;
     }
   }
   if (grp == 0) {
@@ -809,7 +812,8 @@ taot_status launch_dense(const SkParams& p, hipStream_t stream) {
   const unsigned row_grid = (unsigned)((int64_t)B * dense_blocks(R));
   const unsigned col_grid = (unsigned)((int64_t)B * ((R + kDnColBlock - 1) / kDnColBlock));
   const unsigned out_grid = (unsigned)((int64_t)B * ((R + kDnThreads - 1) / kDnThreads));
-  const size_t fix_lds = (size_t)2 * R * sizeof(float);
+  constexpr int32_t kTileRows = kDnFixRows * (kDnThreads / kDnColBlock);
+  const size_t fix_lds = (size_t)2 * ((R + kTileRows - 1) / kTileRows * kTileRows) * sizeof(float);
   for (int32_t it = 1; it <= p.iters; ++it) {
     const taot_status st = it == 1 ? launch_rows<true>(p, kappa, row_grid, stream)
                                    : launch_rows<false>(p, kappa, row_grid, stream);
