@@ -1406,9 +1406,9 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
       for (int g = 0; g < G; ++g) {  // (the rank's count and price come with its key)
         if (g >= sets) continue;
         const int32_t rr = it[g] >= 0 ? r[g] : 0;
-        k[g] = *(volatile uint32_t*)&rk[rr];
-        c0[g] = *(volatile int32_t*)&L.cnt[rr];
-        price[g] = *(volatile double*)&L.price[rr];
+        k[g] = __hip_atomic_load(&rk[rr], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        c0[g] = L.cnt[rr];
+        price[g] = L.price[rr];
       }
 #pragma unroll
       for (int g = 0; g < G; ++g) {
