@@ -1684,84 +1684,140 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
   __syncthreads();
 
   // ---- Phase 2: column-priority iterative matching ---------------------------------
+  // Every thread has one cold rank (nc <= R <= NT).  What bounds a proposal is
+  // the scan of all candidates (two loads and a division each, most ranks of a
+  // wave at once whenever the expert that they all want runs out), so a scan
+  // keeps the rank's best kBestOf candidates with their score terms.  No score
+  // rises after it (spill and spare only fall, the other terms are fixed, a
+  // taken expert stays taken), so every candidate off the list stays at or
+  // below the score of the list's last entry, and behind it in index on a tie:
+  // while the best listed candidate is above that, or level and no later in
+  // index, it is the best of all, and a rank whose list holds all its
+  // candidates never scans again.  The register-capped build has no room for
+  // lists and enough problems in flight to hide a scan's loads (1952 x R = 256:
+  // 3.14 ms a call, 3.3 to 3.9 with lists of 1 to 4); elsewhere the scans are
+  // the matching's time (58 x R = 64: 345 -> 317 us a call).
+  constexpr int kBestOf = WPE > 1 ? 0 : 4, kList = kBestOf > 0 ? kBestOf : 1;
   int32_t used2 = 0;
+  const int32_t rc = tid;
+  double ls[kList], l1[kList], l2[kList];  // scan's scores (descending), terms
+  int32_t le[kList];                       // candidates (-1: none)
+  int32_t lastc = -1;                            // the scan's last entry
+  double bound = INFINITY;                       // its score; -inf: all candidates are listed
+#pragma unroll
+  for (int m = 0; m < kList; ++m) { le[m] = -1; ls[m] = -INFINITY; l1[m] = l2[m] = 0.0; }
   for (int32_t k = 0; k < K; ++k) {
-    for (int32_t rc = tid; rc < nc; rc += NT) { L.matched[rc] = 0; L.prop_e[rc] = -1; }
+    if (rc < nc) {
+      const int32_t pa = k > 0 ? L.assigned[rc * K + k - 1] : -1;  // taken from here on
+#pragma unroll
+      for (int m = 0; m < kBestOf; ++m) le[m] = le[m] == pa ? -1 : le[m];
+      L.matched[rc] = 0;
+      L.prop_e[rc] = -1;
+    }
     __syncthreads();
     for (int32_t inner = 0; inner < nc; ++inner) {
       // Step 1: every unmatched cold rank proposes its best candidate expert
       bool proposed = false;
-      for (int32_t rc = tid; rc < nc; rc += NT) {
-        if (L.matched[rc]) continue;
-        const int32_t sp = L.spare_p[rc];
-        // A losing proposal stands while its expert's q = min(spill, spare) is
-        // unchanged: within a round of k no score rises (spill only falls; an
-        // unmatched rank's spare, its taken set and the other terms are
-        // fixed), so that expert is still the best, and still the lowest
-        // index among the best.  Otherwise the rank scans again.
-        const int32_t pe = L.prop_e[rc];
-        if (pe >= 0) {
-          const int32_t sl = L.spill_p[pe];
-          if ((sl < sp ? sl : sp) == L.qbest[rc]) {
-            proposed = true;
-            continue;
-          }
-        }
-        int32_t best = -1, bq = 0;
-        double bs = -INFINITY;
-        if (sp > 0) {
-          const int32_t r = L.cr[rc];
-          const int32_t* asg = L.assigned + rc * K;
-          const int32_t a0 = k > 0 ? asg[0] : -1, a1 = k > 1 ? asg[1] : -1;
-          const int32_t a2_ = k > 2 ? asg[2] : -1, a3 = k > 3 ? asg[3] : -1;
-          for (int32_t ec0 = 0; ec0 < ne; ec0 += 4) {
-            int32_t sl[4], hh[4];
-            double bp[4];
-            float tt[4];
+      if (rc < nc && !L.matched[rc]) {
+        const int32_t sp = L.spare_p[rc], pe = L.prop_e[rc];
+        // a losing proposal stands while its expert's q = min(spill, spare) is unchanged
+        const int32_t sl0 = pe >= 0 ? L.spill_p[pe] : 0;
+        proposed = pe >= 0 && (sl0 < sp ? sl0 : sp) == L.qbest[rc];
+        if (!proposed) {
+          int32_t best = -1, bq = 0;
+          double bs = -INFINITY;
+          auto offer = [&](int32_t ec, int32_t q, double score) {
+            if (score > bs || (score == bs && ec < best)) { bs = score; best = ec; bq = q; }
+          };
+          if (sp > 0) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const bool in = ec0 + u < ne;
-              sl[u] = in ? L.spill_p[ec0 + u] : 0;
-              hh[u] = in ? L.hce[ec0 + u] : r;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const bool ok = sl[u] > 0 && hh[u] != r;
-              const int64_t o = (int64_t)hh[u] * R + r;
-              bp[u] = ok ? p.Bpref[o] : 0.0;
-              tt[u] = ok ? Tb[o] : 0.f;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const int32_t ec = ec0 + u;
-              if (sl[u] <= 0 || hh[u] == r) continue;
-              bool taken = ec == a0 || ec == a1 || ec == a2_ || ec == a3;
-              for (int32_t kk = 4; kk < k; ++kk) taken |= asg[kk] == ec;
-              if (taken) continue;
-              const double q = (double)(sl[u] < sp ? sl[u] : sp);
-              const double t1 = alpha * bp[u];
-              const double tn = (double)tt[u] / L.den[hh[u]];
-              const double t2 = a2 * tn;
-              const double score = (q + t1) + t2;
-              if (score > bs) { bs = score; best = ec; bq = sl[u] < sp ? sl[u] : sp; }
+            for (int m = 0; m < kBestOf; ++m) {
+              const int32_t sl = le[m] >= 0 ? L.spill_p[le[m]] : 0;
+              const int32_t q = sl < sp ? sl : sp;
+              if (sl > 0) offer(le[m], q, ((double)q + l1[m]) + l2[m]);
             }
           }
+          if (sp > 0 && (kBestOf == 0 || !(bs > bound || (bs == bound && best <= lastc)))) {
+            best = -1;
+            bs = -INFINITY;
+#pragma unroll
+            for (int m = 0; m < kBestOf; ++m) { le[m] = -1; ls[m] = -INFINITY; }
+            const int32_t r = L.cr[rc];
+            const int32_t* asg = L.assigned + rc * K;
+            const int32_t a0 = k > 0 ? asg[0] : -1, a1 = k > 1 ? asg[1] : -1;
+            const int32_t a2_ = k > 2 ? asg[2] : -1, a3 = k > 3 ? asg[3] : -1;
+            for (int32_t ec0 = 0; ec0 < ne; ec0 += 4) {
+              int32_t sl[4], hh[4];
+              double bp[4];
+              float tt[4];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const bool in = ec0 + u < ne;
+                sl[u] = in ? L.spill_p[ec0 + u] : 0;
+                hh[u] = in ? L.hce[ec0 + u] : r;
+              }
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const bool ok = sl[u] > 0 && hh[u] != r;
+                const int64_t o = (int64_t)hh[u] * R + r;
+                bp[u] = ok ? p.Bpref[o] : 0.0;
+                tt[u] = ok ? Tb[o] : 0.f;
+              }
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const int32_t ec = ec0 + u;
+                if (sl[u] <= 0 || hh[u] == r) continue;
+                bool taken = ec == a0 || ec == a1 || ec == a2_ || ec == a3;
+                for (int32_t kk = 4; kk < k; ++kk) taken |= asg[kk] == ec;
+                if (taken) continue;
+                const double q = (double)(sl[u] < sp ? sl[u] : sp);
+                const double t1 = alpha * bp[u];
+                const double tn = (double)tt[u] / L.den[hh[u]];
+                const double t2 = a2 * tn;
+                const double score = (q + t1) + t2;
+                if constexpr (kBestOf == 0) {
+                  if (score > bs) { bs = score; best = ec; bq = sl[u] < sp ? sl[u] : sp; }
+                  continue;
+                }
+                if (!(score > ls[kList - 1])) continue;
+                // in behind the entries that score as much (lower indices)
+                ls[kList - 1] = score;
+                le[kList - 1] = ec;
+                l1[kList - 1] = t1;
+                l2[kList - 1] = t2;
+#pragma unroll
+                for (int m = kList - 1; m > 0; --m) {
+                  const bool up = ls[m] > ls[m - 1];
+                  const double s0 = ls[m - 1], x0 = l1[m - 1], y0 = l2[m - 1];
+                  const int32_t e0 = le[m - 1];
+                  ls[m - 1] = up ? ls[m] : s0; ls[m] = up ? s0 : ls[m];
+                  l1[m - 1] = up ? l1[m] : x0; l1[m] = up ? x0 : l1[m];
+                  l2[m - 1] = up ? l2[m] : y0; l2[m] = up ? y0 : l2[m];
+                  le[m - 1] = up ? le[m] : e0; le[m] = up ? e0 : le[m];
+                }
+              }
+            }
+            if constexpr (kBestOf > 0) {
+              lastc = le[kList - 1];
+              bound = ls[kList - 1];  // (-inf: the list did not fill)
+              best = le[0];
+              bs = ls[0];
+              if (best >= 0) bq = L.spill_p[best] < sp ? L.spill_p[best] : sp;
+            }
+          }
+          L.prop_e[rc] = best;
+          L.prop_s[rc] = bs;
+          L.qbest[rc] = bq;
+          proposed = best >= 0;
         }
-        L.prop_e[rc] = best;
-        L.prop_s[rc] = bs;
-        L.qbest[rc] = bq;
-        proposed |= best >= 0;
       }
       if (!block_or<NT>(proposed, flagbuf, parity)) break;  // nothing can change any more
       // Steps 2-3: each proposed expert keeps its best proposer: max score, then lowest rank
-      for (int32_t rc = tid; rc < nc; rc += NT)
-        if (L.prop_e[rc] >= 0)
-          atomicMax(reinterpret_cast<unsigned long long*>(&L.ekey[L.prop_e[rc]]),
-                    (unsigned long long)ordered_key(L.prop_s[rc]));
+      const int32_t pe = rc < nc ? L.prop_e[rc] : -1;
+      const uint64_t key = pe >= 0 ? ordered_key(L.prop_s[rc]) : 0;
+      if (pe >= 0) atomicMax(reinterpret_cast<unsigned long long*>(&L.ekey[pe]), (unsigned long long)key);
       __syncthreads();
-      for (int32_t rc = tid; rc < nc; rc += NT)
-        if (L.prop_e[rc] >= 0 && ordered_key(L.prop_s[rc]) == L.ekey[L.prop_e[rc]])
-          atomicMin(&L.ewin[L.prop_e[rc]], rc);
+      if (pe >= 0 && key == L.ekey[pe]) atomicMin(&L.ewin[pe], rc);
       __syncthreads();
       // Step 4: winners take g = min(spill, spare) into slot k of their rank
       for (int32_t ec = tid; ec < ne; ec += NT) {

@@ -87,6 +87,34 @@ def test_random(seed, K, gpu):
     _compare(L, home, T32, Bp, Ba, K, label=f"seed{seed}")
 
 
+# The matching keeps the best four candidates of a rank's scan: one to nine
+# candidates (spill > 0), with few distinct loads and costs so that scores tie,
+# ranks that take up to six experts, and a hint with scores that never win.
+@pytest.mark.parametrize("hot", [1, 3, 4, 5, 6, 9])
+@pytest.mark.parametrize("K", [1, 2, 6])
+@pytest.mark.parametrize("hint", ["plan", "zero", "nan"])
+def test_candidate_lists(hot, K, hint, gpu):
+    R, B = (24, 3) if hot < 6 else (90, 2)
+    E = 2 * R
+    rng = np.random.default_rng(hot * 10 + K)
+    home = (np.arange(E) % R).astype(np.int32)
+    ids = np.empty((B, R, 60 * hot + E), np.int32)
+    for b in range(B):
+        heavy = rng.choice(E, size=hot, replace=False)
+        row = np.concatenate([np.repeat(heavy, rng.choice([40, 60], size=hot)), np.arange(E)])
+        ids[b] = np.concatenate([row, np.arange(ids.shape[2] - row.size) % E])
+    L = O.plan_loads(ids, home, E)
+    C = W.cost_matrix_for(R, ("three_tier", 1.0, 3.0, 8.0, 16))
+    T = O.sinkhorn(L.excess.astype(float), L.spare.astype(float), C.astype(float), 0.3, 40).T.astype(np.float32)
+    if hint == "zero":
+        T[:] = 0
+    elif hint == "nan":
+        T[rng.random(T.shape) < 0.2] = np.nan
+        T[rng.random(T.shape) < 0.1] = -np.inf
+    Bp, Ba = O.topology_pref(C)
+    _compare(L, home, T, Bp, Ba, K, label=f"hot {hot} K {K} {hint}")
+
+
 def test_starved_auction_reports_unfilled(gpu):
     L, home, T32, Bp, Ba = _random_instance(99)
     se, sa, X, unfilled = _compare(L, home, T32, Bp, Ba, 2, t_max=2)
