@@ -658,6 +658,9 @@ __global__ void __launch_bounds__(kDnThreads, 8) dense_col_kernel(SkParams p, fl
   if (dj > 0.f) {
     for (int32_t i0 = grp; i0 < R; i0 += kDnFixRows * G) {
       load_tile(i0);
+      // A row without flow has no term, whatever its cost: where c * kappa overflows to -inf,
+      // at() is NaN, which fmaxf passes over and the clamp below turns into 0 (the terms are at
+      // most 1; a select on fu costs 1.2 % of the call, the clamp is part of the exponential).
       auto at = [&](int k) { return fu[i0 + k * G] - c[k] * kappa; };
       float m = mx;
 #pragma unroll
@@ -666,7 +669,7 @@ __global__ void __launch_bounds__(kDnThreads, 8) dense_col_kernel(SkParams p, fl
       asm volatile("" ::: "memory");  // fu is read again: a tile of it would take as many registers as c
       s *= mx == -INFINITY ? 0.f : fexp2(mx - m);
 #pragma unroll
-      for (int k = 0; k < kDnFixRows; ++k) s += fexp2(at(k) - m);
+      for (int k = 0; k < kDnFixRows; ++k) s += __builtin_amdgcn_fmed3f(fexp2(at(k) - m), 0.f, 1.f);
       mx = m;
     }
   }

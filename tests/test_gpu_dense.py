@@ -94,6 +94,28 @@ def test_dense_column_updates(R, gpu):
     _check(a, b, C, 0.02, 40)
 
 
+@pytest.mark.parametrize("R", [15, 16, 100, 257, 300, 512])
+@pytest.mark.parametrize("far", [-1e37, 1e37])
+def test_dense_column_updates_overflowing_costs_without_supply(R, far, gpu):
+    """Finite costs whose multiple log2(e) / eps overflows fp32, in rows
+    without supply only (the last row, which also stands in for the rows of a
+    ragged tile, among them): those rows have no term in an exact column
+    update, whatever their cost."""
+    rng = np.random.default_rng(R)
+    a = np.zeros((2, R), np.float32)
+    b = np.zeros((2, R), np.float32)
+    hot = rng.random((2, R)) < 0.3
+    hot[:, 0], hot[:, R - 1] = True, False
+    a[hot] = rng.integers(1, 3000, size=int(hot.sum()))
+    for p in range(2):
+        nc = int((~hot[p]).sum())
+        b[p, ~hot[p]] = rng.multinomial(int(a[p].sum()), np.full(nc, 1.0 / nc)) + 1
+    C = (rng.uniform(3.0, 4.0, size=(2, R, R)) * rng.uniform(0.8, 1.0, size=(2, 1, R))).astype(np.float32)
+    C[~hot] = np.where(rng.random((int((~hot).sum()), R)) < 0.5, np.float32(far), C[~hot])
+    C[:, R - 1] = far
+    _check(a, b, C, 0.02, 40)
+
+
 def test_dense_stress_shape_per_problem_costs(gpu):
     """The workload-4 shape (R = 1024, the fat-tree costs) with one cost matrix
     per problem, fewer iterations so that the oracle stays quick."""
