@@ -27,6 +27,16 @@ struct Carver {
   }
 };
 
+// ---- LDS of a launch (host) --------------------------------------------------
+// Lets `kernel` be launched with `dynamic` bytes of LDS.  The default limit of
+// 64 KiB counts a kernel's own __shared__ variables too, hence the room left
+// for them.
+constexpr size_t kLdsStaticRoom = 4096;
+inline bool allow_lds(const void* kernel, size_t dynamic) {
+  return dynamic + kLdsStaticRoom <= 65536 ||
+         hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dynamic) == hipSuccess;
+}
+
 // ---- device helpers ---------------------------------------------------------
 // Sum over the 64 lanes of a wave with a fixed butterfly order (deterministic).
 __device__ __forceinline__ float wave_sum(float v) {

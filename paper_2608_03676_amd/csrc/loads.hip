@@ -573,9 +573,7 @@ taot_status launch_plan_loads(const int32_t* ids, int32_t B, int32_t R, int64_t 
   if (pack16) copies = copies16;
   const size_t lds = (size_t)copies * (pack16 ? stride16 : (E + 1)) * sizeof(int32_t);
   auto* hist = pack16 ? histogram_kernel<true> : histogram_kernel<false>;
-  if (lds > 65536 && hipFuncSetAttribute((const void*)hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-                         hipSuccess)
-    return TAOT_ERR_LAUNCH;
+  if (!allow_lds((const void*)hist, lds)) return TAOT_ERR_LAUNCH;
   // counts stored as 16-bit pairs (half the bytes next to the id stream) when
   // the rows are 16-byte aligned and shorter than 2 * 65535 ids
   const bool half = E % 4 == 0 && (reinterpret_cast<uintptr_t>(n) & 15u) == 0 && N < 2 * 65535;

@@ -2066,9 +2066,7 @@ SchWs carve_sched(void* ws, int32_t B, int32_t R, int32_t E, int32_t K) {
 
 template <class CF, int WPE>
 taot_status launch_lds_kernel(const LdsParams& wp, int32_t B, size_t lds, hipStream_t stream) {
-  if (lds > 65536 && hipFuncSetAttribute((const void*)schedule_lds_kernel<CF, WPE>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-    return TAOT_ERR_LAUNCH;
+  if (!allow_lds((const void*)schedule_lds_kernel<CF, WPE>, lds)) return TAOT_ERR_LAUNCH;
   hipLaunchKernelGGL((schedule_lds_kernel<CF, WPE>), dim3((unsigned)B), dim3(CF::kT), lds, stream, wp);
   return hipGetLastError() == hipSuccess ? TAOT_OK : TAOT_ERR_LAUNCH;
 }
@@ -2116,9 +2114,7 @@ taot_status launch_lds_path(const SchParams& p, const SchWs& w, int32_t B, int32
   st = cap ? launch_lds_kernel<CF, CF::kWavesPerEU>(wp, B, slds, stream) : launch_lds_kernel<CF, 1>(wp, B, slds, stream);
   if (st != TAOT_OK) return st;
   if constexpr (CF::kT > kWave) {
-    if (alds > 65536 && hipFuncSetAttribute((const void*)auction_kernel<CF>,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)alds) != hipSuccess)
-      return TAOT_ERR_LAUNCH;
+    if (!allow_lds((const void*)auction_kernel<CF>, alds)) return TAOT_ERR_LAUNCH;
     hipLaunchKernelGGL(auction_kernel<CF>, dim3((unsigned)B), dim3(kWave), alds, stream, wp);
     if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   }
@@ -2153,10 +2149,7 @@ taot_status launch_schedule(const int32_t* n, const int64_t* spill, const int64_
   if (st != TAOT_OK) return st;
   if (!launched) p.fallback = nullptr;  // the general kernel takes every problem
   const size_t lds = (size_t)R * (sizeof(double) + sizeof(uint64_t) + 2 * sizeof(int32_t));
-  if (lds > 65536 && hipFuncSetAttribute((const void*)schedule_kernel,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)lds) != hipSuccess)
-    return TAOT_ERR_LAUNCH;
+  if (!allow_lds((const void*)schedule_kernel, lds)) return TAOT_ERR_LAUNCH;
   hipLaunchKernelGGL(schedule_kernel, dim3((unsigned)sched_grid(B)), dim3(kSchThreads), lds, stream, p);
   return hipGetLastError() == hipSuccess ? TAOT_OK : TAOT_ERR_LAUNCH;
 }

@@ -799,9 +799,7 @@ taot_status launch_wave(const SkParams& p, const TierWs* tier, int32_t* cbad, in
   if (p.R <= 64) return TAOT_OK;
   // the wide problems: at most one workgroup per compute unit at a time
   const size_t lds = wide_lds_bytes(p.R);
-  if (lds > 65536 && hipFuncSetAttribute((const void*)sinkhorn_wide_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)lds) != hipSuccess)
-    return TAOT_ERR_LAUNCH;
+  if (!allow_lds((const void*)sinkhorn_wide_kernel, lds)) return TAOT_ERR_LAUNCH;
   const unsigned grid = (unsigned)std::min<int64_t>(p.B, cus);
   hipLaunchKernelGGL(sinkhorn_wide_kernel, dim3(grid), dim3(kWideThreads), lds, stream, p, wide, counts + 2);
   return hipGetLastError() == hipSuccess ? TAOT_OK : TAOT_ERR_LAUNCH;
@@ -884,19 +882,13 @@ taot_status launch_sinkhorn(const float* a, const float* b, int32_t B, int32_t R
   if (lds_path) {
     p.lds_kt_cap = (int32_t)max_block(R);
     const size_t lds = vec_bytes + (size_t)p.lds_kt_cap * sizeof(float);
-    if (lds > 65536 && hipFuncSetAttribute((const void*)sinkhorn_kernel<false, kSkThreads>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds) != hipSuccess)
-      return TAOT_ERR_LAUNCH;
+    if (!allow_lds((const void*)sinkhorn_kernel<false, kSkThreads>, lds)) return TAOT_ERR_LAUNCH;
     hipLaunchKernelGGL((sinkhorn_kernel<false, kSkThreads>), dim3((unsigned)B), dim3(kSkThreads), lds, stream, p);
     if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   } else {
     p.all_streamed = 1;
   }
-  if (vec_bytes > 65536 && hipFuncSetAttribute((const void*)sinkhorn_kernel<true, kSkStreamThreads>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)vec_bytes) != hipSuccess)
-    return TAOT_ERR_LAUNCH;
+  if (!allow_lds((const void*)sinkhorn_kernel<true, kSkStreamThreads>, vec_bytes)) return TAOT_ERR_LAUNCH;
   hipLaunchKernelGGL((sinkhorn_kernel<true, kSkStreamThreads>), dim3((unsigned)B), dim3(kSkStreamThreads), vec_bytes,
                      stream, p);
   if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;

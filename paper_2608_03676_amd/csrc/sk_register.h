@@ -934,9 +934,7 @@ template <int W, int G>
 taot_status launch_reg_kernel(const SkParams& p, const int32_t* multi, const int32_t* single, const int32_t* counts,
                               hipStream_t stream) {
   const size_t lds = std::max(wave_lds_bytes(p.R, W), (size_t)G * single_lds_bytes(p.R));
-  if (lds > 65536 && hipFuncSetAttribute((const void*)sinkhorn_reg_kernel<W, G>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-    return TAOT_ERR_LAUNCH;
+  if (!allow_lds((const void*)sinkhorn_reg_kernel<W, G>, lds)) return TAOT_ERR_LAUNCH;
   // one workgroup per item at most: B is an upper bound on the items
   hipLaunchKernelGGL((sinkhorn_reg_kernel<W, G>), dim3((unsigned)p.B), dim3(G * kWave), lds, stream, p, multi,
                      single, counts);

@@ -791,9 +791,7 @@ __global__ void __launch_bounds__(NW * kWave) tier_solve_kernel(SkParams p, Tier
 template <int NP, int NW>
 taot_status launch_tier_solve(const SkParams& p, const TierWs& w, int32_t* cls, hipStream_t stream) {
   const size_t lds = tier_lds_bytes(p.R, NP);
-  if (lds > 65536 && hipFuncSetAttribute((const void*)tier_solve_kernel<NP, NW>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-    return TAOT_ERR_LAUNCH;
+  if (!allow_lds((const void*)tier_solve_kernel<NP, NW>, lds)) return TAOT_ERR_LAUNCH;
   hipLaunchKernelGGL((tier_solve_kernel<NP, NW>), dim3((unsigned)((p.B + NP - 1) / NP)), dim3(NW * kWave), lds, stream,
                      p, w, cls);
   return hipGetLastError() == hipSuccess ? TAOT_OK : TAOT_ERR_LAUNCH;

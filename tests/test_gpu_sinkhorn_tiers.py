@@ -111,6 +111,21 @@ def test_batches_of_eight_to_a_group(B, R, sizes, gpu):
     assert not T[5].any() and not T[B - 1].any()
 
 
+@pytest.mark.parametrize("R", [247, 248, 249, 255])
+def test_groups_of_eight_around_64_kib_of_lds(R, gpu):
+    """Eight problems' LDS just below and above 64 KiB: at R = 248 the dynamic
+    part alone is below, with the kernel's own variables it is above."""
+    rng = np.random.default_rng(R)
+    C = _tree_cost(R, (8, 32), (1.0, 3.0, 8.0))
+    a, b = _marginals(rng, R, 1025)
+    T, f, g, st = _run(a, b, C, 0.2, 20)
+    at = [0, 511, 1023, 1024]
+    a64, b64 = a[at].astype(np.float64), b[at].astype(np.float64)
+    ref = O.sinkhorn(a64, b64, C.astype(np.float64), 0.2, 20)
+    sinkhorn_check(T[at], ref.T, a64, b64)
+    assert not st.any()
+
+
 @pytest.mark.parametrize("case", ["five tiers", "not nested", "not symmetric", "one entry", "range", "diagonal range", "slots"])
 def test_other_costs_are_left(case, gpu):
     rng = np.random.default_rng(3)
