@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(NT) sinkhorn_kernel(SkParams p) {
   const float* bd = p.b + pb * R;
   const float* Cb = p.C + pb * p.C_stride;
 
-  if (p.cls && p.cls[pb] == kTierClass) {  // already solved (uniform per block)
+  if (p.cls && p.cls[pb] != 0) {  // the tier path or a register kernel has it (uniform per block)
     if (!STREAM && tid == 0) p.stream_flag[pb] = 0;
     return;
   }
@@ -170,10 +170,6 @@ __global__ void __launch_bounds__(NT) sinkhorn_kernel(SkParams p) {
   // ---- where the Kt block lives ----------------------------------------------
   const int64_t need = (int64_t)nh * nc;
   const bool degenerate = sh_bad || nh == 0 || nc == 0;
-  if (!degenerate && (classify(nh, nc, p.flags) != 0 || wide_class(nh, nc, p.flags) != 0)) {  // a register path owns it
-    if (!STREAM && tid == 0) p.stream_flag[pb] = 0;
-    return;
-  }
   if (!STREAM) {
     const bool to_stream = !degenerate && (need > p.lds_kt_cap || (p.flags & TAOT_SK_FORCE_STREAM));
     if (tid == 0) p.stream_flag[pb] = to_stream ? 1 : 0;
@@ -330,57 +326,10 @@ __global__ void __launch_bounds__(kWave) wave_class_kernel(SkParams p, int32_t* 
   if (lane == 0) cls[pb] = c;
 }
 
-// Multi and single lists of the W-wave kernel (one block), each by descending
-// per-wave work, so that the workgroups dealt out in order start with the
-// heaviest and mix heavy and light work on every compute unit; single groups
-// join problems of similar work.  A counting sort over the per-wave work
-// (below 64): count, exclusive scan from the heaviest down, place.  The order
-// within equal work is whatever the atomics give: it changes the placement
-// of problems on the chip, never a result.  Then the wide problems.
-__global__ void __launch_bounds__(kSkThreads) wave_order_kernel(const int32_t* __restrict__ cls, int32_t B, int32_t W,
-                                                                int32_t* __restrict__ multi,
-                                                                int32_t* __restrict__ single,
-                                                                int32_t* __restrict__ wide,
-                                                                int32_t* __restrict__ counts,
-                                                                const int32_t* __restrict__ left) {
-  __shared__ int32_t bins[3][64];  // multi, single, wide (bin 0) counts, then cursors
-  if (left && left[0] == 0) {  // every problem is solved
-    if (threadIdx.x < 3) counts[threadIdx.x] = 0;
-    return;
-  }
-  for (int q = threadIdx.x; q < 3 * 64; q += kSkThreads) (&bins[0][0])[q] = 0;
-  __syncthreads();
-  auto key = [&](int32_t c, int& list) {
-    if (is_wide_class(c)) { list = 2; return 0; }
-    if (!is_reg_class(c)) { list = -1; return 0; }
-    const int cpl = class_cpl(c), c8 = class_c8(c);
-    list = is_single(W, cpl, c8) ? 1 : 0;
-    return c8_per_wave(W, cpl, c8) * cpl;  // per-wave work, 1 .. 32
-  };
-  for (int32_t b = threadIdx.x; b < B; b += kSkThreads) {
-    int list;
-    const int wk = key(cls[b], list);
-    if (list >= 0) atomicAdd(&bins[list][wk], 1);
-  }
-  __syncthreads();
-  if (threadIdx.x < 3) {
-    const int k = threadIdx.x;
-    int32_t s = 0;
-    for (int wk = 63; wk >= 0; --wk) {  // heaviest first
-      const int32_t n = bins[k][wk];
-      bins[k][wk] = s;
-      s += n;
-    }
-    counts[k] = s;
-  }
-  __syncthreads();
-  for (int32_t b = threadIdx.x; b < B; b += kSkThreads) {
-    int list;
-    const int wk = key(cls[b], list);
-    if (list < 0) continue;
-    const int32_t pos = atomicAdd(&bins[list][wk], 1);
-    (list == 0 ? multi : list == 1 ? single : wide)[pos] = b;
-  }
+// The register kernels' lists, by one block.
+__global__ void __launch_bounds__(kSkThreads)
+wave_order_kernel(const int32_t* cls, int32_t B, RegLists lists) {
+  order_problems<kSkThreads>(cls, B, lists.W, lists.multi, lists.single, lists.wide, lists.counts);
 }
 
 // ---------------------------------------------------------------------------
@@ -763,12 +712,15 @@ sinkhorn_wide_kernel(SkParams p, const int32_t* __restrict__ list, const int32_t
   }
 }
 
+// Up to here a register class holds every problem that is not degenerate.
+constexpr int32_t kRegisterR = 64;
+
 // The register path on the caller's stream: classes, lists, then one
 // register kernel.  W = 4 when every problem can hold four 128-VGPR waves at
 // once (four SIMDs per compute unit, four such waves per SIMD), else 2
 // (TAOT_SK_WAVES_1 forces W = 2, i.e. one wave per problem where it fits).
-// With a tier workspace the tier path runs first and gives the classes.
-taot_status launch_wave(const SkParams& p, const TierWs* tier, int32_t* cbad, int32_t* cls, int32_t* lists,
+// With a tier workspace the tier path runs first and gives classes and lists.
+taot_status launch_wave(const SkParams& p, const TierWs* tier, int32_t* cbad, int32_t* cls, int32_t* list_ws,
                         int32_t* counts, hipStream_t stream) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -776,32 +728,28 @@ taot_status launch_wave(const SkParams& p, const TierWs* tier, int32_t* cbad, in
     return TAOT_ERR_LAUNCH;
   const int64_t cap = (int64_t)cus * 4 * 4;
   const int W = (4 * (int64_t)p.B <= cap && !(p.flags & TAOT_SK_WAVES_1)) ? 4 : 2;
+  const RegLists lists{W, list_ws, list_ws + p.B, list_ws + 2 * (int64_t)p.B, counts};
   if (tier) {
-    const taot_status st = launch_tier(p, *tier, cls, cbad, stream);
+    const taot_status st = launch_tier(p, *tier, cls, cbad, lists, stream);
     if (st != TAOT_OK) return st;
   } else {
     hipLaunchKernelGGL(wave_class_kernel, dim3((unsigned)p.B), dim3(kWave), 0, stream, p, cls);
     if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
+    hipLaunchKernelGGL(wave_order_kernel, dim3(1), dim3(kSkThreads), 0, stream, cls, p.B, lists);
+    if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   }
-  int32_t* multi = lists;
-  int32_t* single = lists + p.B;
-  int32_t* wide = lists + 2 * (int64_t)p.B;
-  hipLaunchKernelGGL(wave_order_kernel, dim3(1), dim3(kSkThreads), 0, stream, cls, p.B, W, multi, single, wide,
-                     counts, tier ? tier->left : nullptr);
-  if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   // two-wave shapes run in eight-wave groups while their LDS slices fit 64 KB
   const bool g8 = 8 * single_lds_bytes(p.R) <= 65536;
-  const taot_status st = W == 4 ? launch_reg_w4g4(p, multi, single, counts, stream)
-                         : g8   ? launch_reg_w2g8(p, multi, single, counts, stream)
-                                : launch_reg_w2g2(p, multi, single, counts, stream);
+  const taot_status st = W == 4 ? launch_reg_w4g4(p, lists.multi, lists.single, counts, stream)
+                         : g8   ? launch_reg_w2g8(p, lists.multi, lists.single, counts, stream)
+                                : launch_reg_w2g2(p, lists.multi, lists.single, counts, stream);
   if (st != TAOT_OK) return st;
-  // up to 64 ranks a register class holds every problem
-  if (p.R <= 64) return TAOT_OK;
+  if (p.R <= kRegisterR) return TAOT_OK;
   // the wide problems: at most one workgroup per compute unit at a time
   const size_t lds = wide_lds_bytes(p.R);
   if (!allow_lds((const void*)sinkhorn_wide_kernel, lds)) return TAOT_ERR_LAUNCH;
   const unsigned grid = (unsigned)std::min<int64_t>(p.B, cus);
-  hipLaunchKernelGGL(sinkhorn_wide_kernel, dim3(grid), dim3(kWideThreads), lds, stream, p, wide, counts + 2);
+  hipLaunchKernelGGL(sinkhorn_wide_kernel, dim3(grid), dim3(kWideThreads), lds, stream, p, lists.wide, counts + 2);
   return hipGetLastError() == hipSuccess ? TAOT_OK : TAOT_ERR_LAUNCH;
 }
 
@@ -813,7 +761,7 @@ struct SkWs {
   int32_t* cls;     // [B] register class
   int32_t* lists;   // [3][B] register problems: multi, single, wide
   int32_t* counts;  // [3]
-  int32_t* cbad;    // [B or 1][scan_chunks(R)] chunk marks of the cost scan (tier path: [R])
+  int32_t* cbad;    // [B or 1][scan_chunks(R)] chunk marks of the cost scan (tier path: [1])
   float* kt;
   int64_t kt_stride;
   float* dn;        // [B][dn_stride] state of the dense streamed iterate
@@ -829,13 +777,12 @@ SkWs carve(void* ws, int32_t B, int32_t R) {
   w.cls = c.take<int32_t>((size_t)B);
   w.lists = c.take<int32_t>((size_t)3 * B);
   w.counts = c.take<int32_t>(3);
-  w.cbad = c.take<int32_t>(std::max((size_t)B * scan_chunks(R), (size_t)R));
+  w.cbad = c.take<int32_t>((size_t)B * scan_chunks(R));
   w.kt_stride = round_up((int64_t)R * R, 64);
   w.kt = c.take<float>((size_t)B * w.kt_stride);
   w.dn_stride = round_up((int64_t)dense_state_floats(R), 64);
   w.dn = c.take<float>((size_t)B * w.dn_stride);
   w.tier.tree = c.take<TierTree>(1);
-  w.tier.left = c.take<int32_t>(1);
   w.tier.rv = c.take<float4>((size_t)R);
   w.tier.rcnt = c.take<int4>((size_t)R);
   w.tier.rlab = c.take<int4>((size_t)R);
@@ -864,7 +811,7 @@ taot_status launch_sinkhorn(const float* a, const float* b, int32_t B, int32_t R
   // a shared cost matrix may be a tree of tiers (TAOT_SK_WAVES_1 asks for the register path)
   const bool tier = wave && C_stride == 0 && !(flags & TAOT_SK_WAVES_1);
   if (tier) {
-    p.cchunks = R;  // the tier prepass marks rows
+    p.cchunks = 1;  // the tier prepass gives one mark
   } else {
     const int64_t mats = C_stride ? B : 1;
     hipLaunchKernelGGL(cost_scan_kernel, dim3((unsigned)(mats * p.cchunks)), dim3(kScanThreads), 0, stream, C,
@@ -885,6 +832,7 @@ taot_status launch_sinkhorn(const float* a, const float* b, int32_t B, int32_t R
     if (!allow_lds((const void*)sinkhorn_kernel<false, kSkThreads>, lds)) return TAOT_ERR_LAUNCH;
     hipLaunchKernelGGL((sinkhorn_kernel<false, kSkThreads>), dim3((unsigned)B), dim3(kSkThreads), lds, stream, p);
     if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
+    if (wave && R <= kRegisterR) return TAOT_OK;  // only degenerate problems were left, and none is streamed
   } else {
     p.all_streamed = 1;
   }

@@ -37,8 +37,7 @@ struct SkParams {
 
 // What the tier path finds out about a shared cost matrix, in the workspace.
 struct TierTree {
-  int32_t ok;        // the row scans describe a tree of tiers
-  int32_t mismatch;  // some entry of C disagrees with it
+  int32_t ok;        // C is a tree of tiers that some problem is solved on
   int32_t nbits;     // slots = 2^nbits
   int32_t cut[2];    // address bits below which two slots are in tier 2 (3) at most
   float c[4];        // costs of the tiers, ascending
@@ -48,11 +47,10 @@ struct TierTree {
 };
 struct TierWs {
   TierTree* tree;
-  int32_t* left;   // [1] 1 = some problem is left to the other kernels
   float4* rv;      // [R] distinct off-diagonal costs of a row, ascending, then +inf
   int4* rcnt;      // [R] how often each occurs
   int4* rlab;      // [R] lowest rank within that cost
-  int4* rmore;     // [R] number of costs, next rank at the smallest, diagonal (bits), non-finite
+  int4* rmore;     // [R] number of costs, next rank at the smallest, diagonal (bits), 1: not finite, 2: unlike rlab's rows
   double* k0;      // [R] sum_j exp(-(C_ij - c_1) / eps)
   int32_t* slot;   // [R]
   int32_t* next;   // [R] the next rank of the same leaf, or R
@@ -181,6 +179,52 @@ static_assert(shapes_covered(), "every register class must map to a compiled sha
 __device__ __forceinline__ int class_cpl(int32_t cls) { return 1 << ((cls - 1) / 8); }
 __device__ __forceinline__ int class_c8(int32_t cls) { return (cls - 1) % 8 + 1; }
 
+// Multi and single lists of the W-wave kernel, by one block of NT threads, each
+// by descending per-wave work, so that the workgroups dealt out in order start
+// with the heaviest and mix heavy and light work on every compute unit; single
+// groups join problems of similar work.  A counting sort over the per-wave work
+// (below 64): count, exclusive scan from the heaviest down, place.  The order
+// within equal work is whatever the atomics give: it changes the placement
+// of problems on the chip, never a result.  Then the wide problems.
+template <int NT>
+__device__ void order_problems(const int32_t* cls, int32_t B, int32_t W, int32_t* multi, int32_t* single,
+                               int32_t* wide, int32_t* counts) {
+  __shared__ int32_t bins[3][64];  // multi, single, wide (bin 0) counts, then cursors
+  for (int q = threadIdx.x; q < 3 * 64; q += NT) (&bins[0][0])[q] = 0;
+  __syncthreads();
+  auto key = [&](int32_t c, int& list) {
+    if (is_wide_class(c)) { list = 2; return 0; }
+    if (!is_reg_class(c)) { list = -1; return 0; }
+    const int cpl = class_cpl(c), c8 = class_c8(c);
+    list = is_single(W, cpl, c8) ? 1 : 0;
+    return c8_per_wave(W, cpl, c8) * cpl;  // per-wave work, 1 .. 32
+  };
+  for (int32_t b = threadIdx.x; b < B; b += NT) {
+    int list;
+    const int wk = key(cls[b], list);
+    if (list >= 0) atomicAdd(&bins[list][wk], 1);
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    const int k = threadIdx.x;
+    int32_t s = 0;
+    for (int wk = 63; wk >= 0; --wk) {  // heaviest first
+      const int32_t n = bins[k][wk];
+      bins[k][wk] = s;
+      s += n;
+    }
+    counts[k] = s;
+  }
+  __syncthreads();
+  for (int32_t b = threadIdx.x; b < B; b += NT) {
+    int list;
+    const int wk = key(cls[b], list);
+    if (list < 0) continue;
+    const int32_t pos = atomicAdd(&bins[list][wk], 1);
+    (list == 0 ? multi : list == 1 ? single : wide)[pos] = b;
+  }
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
   // every lane has a source lane for the patterns used here, so bound_ctrl
@@ -282,10 +326,20 @@ taot_status launch_reg_w2g8(const SkParams& p, const int32_t* multi, const int32
                             hipStream_t stream);
 taot_status launch_reg_w2g2(const SkParams& p, const int32_t* multi, const int32_t* single, const int32_t* counts,
                             hipStream_t stream);
-// The tier path: the prepass over a shared cost matrix (also its validation,
-// one mark per row in cbad), then every problem it can take solved and the
-// class of every other in cls (w.left[0] = 1 if there is one).
-taot_status launch_tier(const SkParams& p, const TierWs& w, int32_t* cls, int32_t* cbad, hipStream_t stream);
+// The problems of the register kernels: their lists, counts [3] (multi, single,
+// wide) and the waves W of a multi-wave problem.
+struct RegLists {
+  int32_t W;
+  int32_t* multi;
+  int32_t* single;
+  int32_t* wide;
+  int32_t* counts;
+};
+// The tier path: the prepass over a shared cost matrix (also its validation:
+// cbad[0] = 1 if it holds a non-finite entry) and the problems' classes, then
+// every problem it can take solved; cls and the lists hold the others.
+taot_status launch_tier(const SkParams& p, const TierWs& w, int32_t* cls, int32_t* cbad, const RegLists& lists,
+                        hipStream_t stream);
 // The dense streamed iterate (TAOT_SK_DENSE) and its per-problem state in the
 // streamed-plan storage of the workspace.
 taot_status launch_dense(const SkParams& p, hipStream_t stream);

@@ -32,11 +32,11 @@
 // bounds the iteration; the plan's R x R stores bound the rest.
 //
 // Measured (whole call, MI355X, fp32 kernels before -> this path): 58 problems
-// of R = 64, 500 iterations 207 -> 74 us; 1952 of R = 256, 1000 iterations
-// 1850 -> 217 us; 64 of R = 1024, 2000 iterations 5150 -> 480 us.  Per
+// of R = 64, 500 iterations 207 -> 70 us; 1952 of R = 256, 1000 iterations
+// 1850 -> 213 us; 64 of R = 1024, 2000 iterations 5150 -> 466 us.  Per
 // iteration and wave 0.08 us with 8 slots, 0.13 with 32, 0.19 with 128; R = 256
 // writes its 512 MB of plans in about 110 us, most of it while the waves
-// iterate.  A shared matrix that is no such tree pays the prepass, 4 to 10 us.
+// iterate.
 //
 // Any other shared matrix (more tiers, groups that do not nest, a tier beyond
 // 200 eps), and any problem with a rank on both sides, with marginals outside
@@ -54,30 +54,45 @@ constexpr double kTierRange = 200.0;              // |C_ij - c_1| <= kTierRange 
 constexpr double kTierDrift = 40.0;               // iters * log(demand / supply) at most
 constexpr float kTierMassLo = 0x1p-60f, kTierMassHi = 0x1p60f;
 constexpr int kTreeThreads = 1024;
-constexpr int kTierFusedR = 128;   // up to here one block does the whole prepass
-constexpr int kTierSmallR = 256;   // up to here a plan row is one or two stores of a wave
+constexpr int kTierSmallR = 256;  // up to here a plan row is one or two stores of a wave
 
 // ---- prepass, once per call ---------------------------------------------------
+//
+// Two launches.  tier_rows_kernel scans every row of C, a wave each, and beside
+// them gives every problem its class; tier_tree_kernel (one block) joins the
+// rows into the tree, if they describe one and some problem can be solved on it,
+// and lists the problems that are left.  They take the place of the cost scan,
+// the classes and the order of the other paths, so that a matrix or problems
+// that are not for this path lose nothing by it: 58 problems of R = 64, 200
+// iterations, costs that are no tree 121.8 us without this path, 118.9 with it
+// (125.3 with a prepass in one block and the classes behind it); a tree with one
+// other entry 121.9 and 118.4 (135.1); more demand than supply 171.9 and 168.1
+// (184.4).
+//
+// Why the rows' own checks suffice.  Let N_l(i) be i and the ranks within c_l of
+// it.  C is a tree of its tiers if and only if N_l is a partition for every l.
+// Row i is compared in full with the row of the lowest rank x of N_l(i) at each
+// cost of its own: the same set there.  So N_l(i) is within N_l(x).  The tree
+// block then checks that x is the lowest rank of its own set and that the ranks
+// which name x are as many as N_l(i) holds: those ranks lie within N_l(x), are as
+// many as it, and so are it; and N_l(i), within it and as large, is the same set.
 
-// Scan of row i by one wave, KR entries per lane held in registers: non-finite
-// entries (the chunk mark of the cost validation, one chunk per row), the
-// row's distinct off-diagonal costs in ascending order (num = 5: more than
-// four), for each its multiplicity and the lowest rank at most that far (i
-// itself included), and the next rank after i at the smallest cost.  Returns
-// whether the row has more than four; `quick` (some other row has) only looks
-// for non-finite entries.
+// A problem's class in the prepass: that of the other kernels, and whether the
+// tier path can take it.
+constexpr int32_t kTierEligible = 1 << 8;
+
 template <int KR>
-__device__ __forceinline__ void tier_load(const float* __restrict__ C, int32_t R, int32_t i, float (&c)[KR], float& diag) {
+__device__ __forceinline__ void tier_row(const TierWs& w, const float* __restrict__ C, int32_t R, int32_t i) {
+  // Scan of row i by one wave, KR entries per lane held in registers: non-finite
+  // entries, the row's distinct off-diagonal costs in ascending order (num = 5:
+  // more than four), for each its multiplicity and the lowest rank at most that
+  // far (i itself included), and the next rank after i at the smallest cost.
   const int lane = threadIdx.x & (kWave - 1);
   const float* row = C + (int64_t)i * R;
+  float c[KR];
 #pragma unroll
   for (int k = 0; k < KR; ++k) c[k] = lane + kWave * k < R ? row[lane + kWave * k] : INFINITY;
-  diag = row[i];
-}
-template <int KR>
-__device__ __forceinline__ bool tier_row(const TierWs& w, int32_t R, int32_t i, float (&c)[KR], float diag,
-                                         int32_t* __restrict__ cbad, bool quick) {
-  const int lane = threadIdx.x & (kWave - 1);
+  const float diag = row[i];
   bool bad = false;
 #pragma unroll
   for (int k = 0; k < KR; ++k) {
@@ -98,7 +113,7 @@ __device__ __forceinline__ bool tier_row(const TierWs& w, int32_t R, int32_t i, 
   int32_t num = 0, nxt = R;
 #pragma unroll
   for (int l = 0; l <= kTierLevels; ++l) {
-    if (any_bad || quick) break;
+    if (any_bad) break;
     float next = INFINITY;
 #pragma unroll
     for (int k = 0; k < KR; ++k) next = fminf(next, c[k] > cur ? c[k] : INFINITY);
@@ -124,23 +139,97 @@ __device__ __forceinline__ bool tier_row(const TierWs& w, int32_t R, int32_t i, 
     rcnt[l] = cnt;
     rlab[l] = lab;
   }
+  // the rows of the sets' lowest ranks (the last set holds every rank)
+  bool differ = false;
+#pragma unroll
+  for (int l = 0; l + 1 < kTierLevels; ++l) {
+    if (any_bad || num > kTierLevels || l + 1 >= num || rlab[l] == i) continue;
+    const float* other = C + (int64_t)rlab[l] * R;
+    float x[KR];
+#pragma unroll
+    for (int k = 0; k < KR; ++k) x[k] = lane + kWave * k < R ? other[lane + kWave * k] : INFINITY;
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+      const int32_t j = lane + kWave * k;
+      differ |= (j == i || c[k] <= rv[l]) != (j == rlab[l] || x[k] <= rv[l]);
+    }
+  }
+  const bool any_differ = __ballot(differ) != 0;
   if (lane == 0) {
     w.rv[i] = float4{rv[0], rv[1], rv[2], rv[3]};
     w.rcnt[i] = int4{rcnt[0], rcnt[1], rcnt[2], rcnt[3]};
     w.rlab[i] = int4{rlab[0], rlab[1], rlab[2], rlab[3]};
-    w.rmore[i] = int4{num, nxt, __float_as_int(diag), any_bad ? 1 : 0};
-    cbad[i] = any_bad ? 1 : 0;
+    w.rmore[i] = int4{num, nxt, __float_as_int(diag), (any_bad ? 1 : 0) | (any_differ ? 2 : 0)};
   }
-  return num > kTierLevels;
+}
+
+// Problem pb by one wave: validity, mass, supports.
+__device__ __forceinline__ int32_t tier_class(const SkParams& p, int64_t pb) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int32_t R = p.R;
+  const float* a = p.a + pb * R;
+  const float* bd = p.b + pb * R;
+  double sa = 0.0, sd = 0.0;
+  int32_t nh = 0, nc = 0;
+  bool bad = false, other = false;
+  constexpr int kAtOnce = 4;  // loads in flight: one wave reads it all
+  for (int32_t base = 0; base < R; base += kAtOnce * kWave) {
+    float x[kAtOnce], y[kAtOnce];
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) {
+      const int32_t i = base + kWave * k + lane;
+      x[k] = i < R ? a[i] : 0.f;
+      y[k] = i < R ? bd[i] : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) {
+      const float ai = x[k], bi = y[k];
+      bad |= !(ai >= 0.f && ai <= 3.402823466e38f) || !(bi >= 0.f && bi <= 3.402823466e38f);
+      other |= (ai > 0.f && bi > 0.f) || (ai > 0.f && !(ai >= kTierMassLo && ai <= kTierMassHi)) ||
+               (bi > 0.f && !(bi >= kTierMassLo && bi <= kTierMassHi));
+      nh += (int32_t)__popcll(__ballot(ai > 0.f));
+      nc += (int32_t)__popcll(__ballot(bi > 0.f));
+      sa += (double)ai;
+      sd += (double)bi;
+    }
+  }
+  if (__ballot(bad) != 0) return 0;
+  sa = wave_sum_d(sa);
+  sd = wave_sum_d(sd);
+  const double gamma = fmin(1.0, sd / fmax(sa, kEps0));
+  const double surplus = sd / (gamma * sa);  // >= 1; its powers are the drift of the scalings
+  const bool ok = __ballot(other) == 0 && nh > 0 && nc > 0 && (double)p.iters * (surplus - 1.0) <= kTierDrift;
+  int c = classify(nh, nc, p.flags);
+  if (c == 0) c = wide_class(nh, nc, p.flags);
+  return c | (ok ? kTierEligible : 0);
+}
+
+__global__ void __launch_bounds__(kSkThreads)
+tier_rows_kernel(SkParams p, TierWs w, int32_t row_blocks, int32_t* __restrict__ cls) {
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int32_t R = p.R;
+  if ((int32_t)blockIdx.x >= row_blocks) {
+    const int64_t pb = (int64_t)((int32_t)blockIdx.x - row_blocks) * kSkWaves + wid;
+    if (pb >= p.B) return;
+    const int32_t c = tier_class(p, pb);
+    if ((threadIdx.x & (kWave - 1)) == 0) cls[pb] = c;
+    return;
+  }
+  const int32_t i = (int32_t)blockIdx.x * kSkWaves + wid;
+  if (i >= R) return;
+  if (R <= kWave) tier_row<1>(w, p.C, R, i);
+  else if (R <= 4 * kWave) tier_row<4>(w, p.C, R, i);
+  else if (R <= 16 * kWave) tier_row<16>(w, p.C, R, i);
+  else tier_row<TAOT_MAX_RANKS / kWave>(w, p.C, R, i);
 }
 
 // The tree of the row scans, by one block of kTreeThreads: the tiers, the
 // slots, the members of each slot, the butterfly weights and the first row
-// update's sums.  Sets tree->ok (0: not such a tree); whether every entry of C
-// agrees with it is for tier_check_row to say.
-__device__ void tier_tree(const TierWs& w, int32_t R, float eps) {
+// update's sums.  Returns (to every thread) whether C is such a tree.
+__device__ bool tier_tree(const TierWs& w, int32_t R, float eps) {
   __shared__ int16_t labs[kTierLevels][TAOT_MAX_RANKS];
   __shared__ int16_t leafof[TAOT_MAX_RANKS];
+  __shared__ int32_t named[kTierLevels - 1][TAOT_MAX_RANKS];  // ranks that name this one as their set's lowest
   __shared__ int16_t rep[kTierSlots], idx[3][kTierSlots], slot_of_leaf[kTierSlots];
   __shared__ short4 pack[kTierSlots];
   __shared__ int32_t wave_n[kTreeThreads / kWave], widest[3], sh_bad;
@@ -170,13 +259,11 @@ __device__ void tier_tree(const TierWs& w, int32_t R, float eps) {
       more[k] = w.rmore[i];
     }
   }
-  if (tid == 0) {
-    sh_bad = 0;
-    tree->ok = 0;
-    tree->mismatch = 0;
-    w.left[0] = 0;
-  }
+  if (tid == 0) sh_bad = 0;
   if (tid < 3) widest[tid] = 0;
+  for (int32_t i = tid; i < R; i += kTreeThreads)
+#pragma unroll
+    for (int l = 0; l + 1 < kTierLevels; ++l) named[l][i] = 0;
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kRows; ++k)
@@ -205,15 +292,16 @@ __device__ void tier_tree(const TierWs& w, int32_t R, float eps) {
     if (l == kTierLevels) break;
     c[l] = cur = next;
   }
-  if (any_bad() || L < 1 || L > kTierLevels) return;
+  if (any_bad() || L < 1 || L > kTierLevels) return false;
   const double inv = 1.0 / (double)eps;
 #pragma unroll
   for (int t = 1; t < kTierLevels; ++t) c[t] = t < L ? c[t] : c[t - 1];
   const double c1 = (double)c[0];
-  if (((double)c[kTierLevels - 1] - c1) * inv > kTierRange) return;
+  if (((double)c[kTierLevels - 1] - c1) * inv > kTierRange) return false;
   // weights exp(-(c_l - c_1) / eps), and the labels: the lowest rank of each
   // rank's group at each level
   double m[kTierLevels];
+  int32_t held[kRows][kTierLevels - 1];  // ranks of this thread's rows' sets (of the levels below the last)
 #pragma unroll
   for (int l = 0; l < kTierLevels; ++l) m[l] = exp(-((double)c[l] - c1) * inv);
 #pragma unroll
@@ -230,20 +318,39 @@ __device__ void tier_tree(const TierWs& w, int32_t R, float eps) {
 #pragma unroll
     for (int l = 0; l < kTierLevels; ++l) {
       lab[l] = i;
+      int32_t in = 1;
       bool first = true;  // tiers past the last repeat it: count it once
       if (l > 0) first = c[l] != c[l - 1];
 #pragma unroll
       for (int t = 0; t < kTierLevels; ++t) {
-        if (v[t] <= c[l]) lab[l] = g[t];
+        if (v[t] <= c[l]) {
+          lab[l] = g[t];
+          in += n[t];
+        }
         if (first && v[t] == c[l]) k0 += (double)n[t] * m[l];
       }
       labs[l][i] = (int16_t)lab[l];
+      if (l + 1 < kTierLevels) {
+        held[k][l] = in;
+        if (l + 1 < L) atomicAdd(&named[l][lab[l]], 1);
+      }
     }
     leafof[i] = -1;
     w.k0[i] = k0;
     w.next[i] = v[0] == c[0] ? more[k].y : R;
   }
-  if (any_bad()) return;
+  if (any_bad()) return false;
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) {
+    const int32_t i = tid + kTreeThreads * k;
+    if (i >= R) break;
+#pragma unroll
+    for (int l = 0; l + 1 < kTierLevels; ++l) {
+      const int32_t x = labs[l][i];
+      if (l + 1 < L && (labs[l][x] != x || named[l][x] != held[k][l])) sh_bad = 1;
+    }
+  }
+  if (any_bad()) return false;
   // the leaves (innermost groups) by their lowest rank, ascending
   int32_t Q = 0;
   for (int32_t base = 0; base < R; base += kTreeThreads) {
@@ -267,7 +374,7 @@ __device__ void tier_tree(const TierWs& w, int32_t R, float eps) {
     Q += tot;
     __syncthreads();
   }
-  if (Q > kTierSlots) return;
+  if (Q > kTierSlots) return false;
   // index of each group among its siblings, in the order of their lowest ranks
   if (tid < Q) {
     const short4 me = pack[tid];
@@ -297,7 +404,7 @@ __device__ void tier_tree(const TierWs& w, int32_t R, float eps) {
     bits[l] = widest[l] > 0 ? 32 - __builtin_clz((unsigned)widest[l]) : 0;
     nb += bits[l];
   }
-  if (nb > kTierMaxBits) return;
+  if (nb > kTierMaxBits) return false;
   if (tid < (1 << nb)) w.head[tid] = R;  // a slot without a leaf
   __syncthreads();
   if (tid < Q) {
@@ -311,13 +418,13 @@ __device__ void tier_tree(const TierWs& w, int32_t R, float eps) {
       w.head[sl] = me.x;
     }
   }
-  if (any_bad()) return;
+  if (any_bad()) return false;
   for (int32_t i = tid; i < R; i += kTreeThreads) {
     const int32_t q = leafof[labs[0][i]];
     if (q < 0) sh_bad = 1;
     else w.slot[i] = slot_of_leaf[q];
   }
-  if (any_bad()) return;
+  if (any_bad()) return false;
   if (tid == 0) {
     tree->nbits = nb;
     tree->cut[0] = L >= 3 ? bits[0] : nb;
@@ -340,106 +447,47 @@ __device__ void tier_tree(const TierWs& w, int32_t R, float eps) {
         if (l < L && t == at[l]) wt[t] += m[l] - (l + 1 < L ? m[l + 1 < kTierLevels ? l + 1 : l] : 0.0);
 #pragma unroll
     for (int t = 0; t <= kTierMaxBits; ++t) tree->w[t] = wt[t];
-    tree->ok = 1;
   }
+  return true;
 }
 
-// Compares rows i, i + step, .. of C with the tree (one wave), four rows'
-// loads in flight: the cost between two ranks is the tier of the highest
-// address bit in which their slots differ.
-__device__ __forceinline__ void tier_check_rows(const TierWs& w, const float* __restrict__ C, int32_t R, int32_t i0,
-                                                int32_t step) {
-  constexpr int kAtOnce = 4;
-  const int lane = threadIdx.x & (kWave - 1);
-  TierTree* tree = w.tree;
-  const int32_t lim1 = 1 << tree->cut[0], lim2 = 1 << tree->cut[1];
-  const float c0 = tree->c[0], c1 = tree->c[1], c2 = tree->c[2], c3 = tree->c[3];
-  bool bad = false;
-  for (int32_t i = i0; i < R; i += step * kAtOnce) {
-    int32_t si[kAtOnce];
-#pragma unroll
-    for (int u = 0; u < kAtOnce; ++u) si[u] = w.slot[min(i + step * u, R - 1)];
-    for (int32_t j = lane; j < R; j += kWave) {
-      const int32_t sj = w.slot[j];
-      float x[kAtOnce];
-#pragma unroll
-      for (int u = 0; u < kAtOnce; ++u) x[u] = C[(int64_t)min(i + step * u, R - 1) * R + j];
-#pragma unroll
-      for (int u = 0; u < kAtOnce; ++u) {
-        const int32_t d = si[u] ^ sj;
-        const float e = d == 0 ? c0 : d < lim1 ? c1 : d < lim2 ? c2 : c3;
-        bad |= j != min(i + step * u, R - 1) && x[u] != e;
-      }
-    }
-  }
-  if (__ballot(bad) != 0 && lane == 0) tree->mismatch = 1;
-}
-
-// The rows wid, wid + 16, .. of a block of kTreeThreads, all loaded before the
-// first is scanned.
-template <int KR>
-__device__ __forceinline__ void tier_block_rows(const TierWs& w, const float* __restrict__ C, int32_t R,
-                                                int32_t* __restrict__ cbad, int32_t* many) {
-  constexpr int kWaves = kTreeThreads / kWave;
-  constexpr int kRows = KR * kWave / kWaves;
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  float c[kRows][KR], diag[kRows];
-#pragma unroll
-  for (int u = 0; u < kRows; ++u) tier_load(C, R, min(wid + kWaves * u, R - 1), c[u], diag[u]);
-#pragma unroll
-  for (int u = 0; u < kRows; ++u) {
-    const int32_t i = wid + kWaves * u;
-    if (i < R && tier_row(w, R, i, c[u], diag[u], cbad, *(volatile int32_t*)many != 0)) *many = 1;
-  }
-}
-template <int KR>
-__device__ __forceinline__ void tier_one_row(const TierWs& w, const float* __restrict__ C, int32_t R, int32_t i,
-                                             int32_t* __restrict__ cbad) {
-  float c[KR], diag;
-  tier_load(C, R, i, c, diag);
-  tier_row(w, R, i, c, diag, cbad, false);
-}
-
-// The whole prepass in one block, for R <= kTierFusedR.
+// The tree, the final classes and the register kernels' lists.
 __global__ void __launch_bounds__(kTreeThreads)
-tier_prepass_kernel(TierWs w, const float* __restrict__ C, int32_t R, float eps, int32_t* __restrict__ cbad) {
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  __shared__ int32_t many;  // a row has too many costs: there is no tree
-  if (threadIdx.x == 0) many = 0;
+tier_tree_kernel(SkParams p, TierWs w, int32_t* cls, int32_t* __restrict__ cbad, RegLists lists) {
+  __shared__ int32_t found;
+  constexpr int kElig = 1, kBad = 2, kNoTree = 4;
+  const int tid = threadIdx.x;
+  const int32_t B = p.B, R = p.R;
+  if (tid == 0) found = 0;
   __syncthreads();
-  static_assert(kTierFusedR <= 2 * kWave, "two entries of a row per lane");
-  if (R <= kWave) tier_block_rows<1>(w, C, R, cbad, &many);
-  else tier_block_rows<2>(w, C, R, cbad, &many);
+  int f = 0;
+  for (int32_t b = tid; b < B; b += kTreeThreads) f |= (cls[b] & kTierEligible) ? kElig : 0;
+  for (int32_t i = tid; i < R; i += kTreeThreads) {
+    const int4 m = w.rmore[i];
+    f |= ((m.w & 1) ? kBad : 0) | ((m.w & 2) || m.x > kTierLevels ? kNoTree : 0);
+  }
+  f = (__ballot(f & kElig) ? kElig : 0) | (__ballot(f & kBad) ? kBad : 0) | (__ballot(f & kNoTree) ? kNoTree : 0);
+  if ((tid & (kWave - 1)) == 0 && f) atomicOr(&found, f);
   __syncthreads();
-  if (many) {
-    if (threadIdx.x == 0) {
-      w.tree->ok = 0;
-      w.left[0] = 0;
-    }
+  f = found;
+  bool ok = f == kElig;
+  if (ok) ok = tier_tree(w, R, p.eps);
+  if (tid == 0) {
+    w.tree->ok = ok ? 1 : 0;
+    cbad[0] = (f & kBad) ? 1 : 0;
+  }
+  bool left = false;
+  for (int32_t b = tid; b < B; b += kTreeThreads) {  // (a thread reads back below what it writes here)
+    const int32_t c = cls[b];
+    const int32_t k = ok && (c & kTierEligible) ? kTierClass : (f & kBad) ? 0 : c & (kTierEligible - 1);
+    cls[b] = k;
+    left |= k != kTierClass;
+  }
+  if (__syncthreads_or(left) == 0) {  // every problem is solved here
+    if (tid < 3) lists.counts[tid] = 0;
     return;
   }
-  tier_tree(w, R, eps);
-  __syncthreads();
-  if (w.tree->ok == 0) return;
-  tier_check_rows(w, C, R, wid, kTreeThreads / kWave);
-}
-// The same in three launches for larger R (a row per wave over the chip).
-__global__ void __launch_bounds__(kSkThreads)
-tier_rows_kernel(TierWs w, const float* __restrict__ C, int32_t R, int32_t* __restrict__ cbad) {
-  const int32_t i = blockIdx.x * kSkWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (i >= R) return;
-  if (R <= 4 * kWave) tier_one_row<4>(w, C, R, i, cbad);
-  else if (R <= 16 * kWave) tier_one_row<16>(w, C, R, i, cbad);
-  else tier_one_row<TAOT_MAX_RANKS / kWave>(w, C, R, i, cbad);
-}
-__global__ void __launch_bounds__(kTreeThreads)
-tier_tree_kernel(TierWs w, int32_t R, float eps) {
-  tier_tree(w, R, eps);
-}
-__global__ void __launch_bounds__(kSkThreads)
-tier_check_kernel(TierWs w, const float* __restrict__ C, int32_t R) {
-  const int32_t i = blockIdx.x * kSkWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (w.tree->ok != 0) tier_check_rows(w, C, R, i, gridDim.x * kSkWaves);
+  order_problems<kTreeThreads>(cls, B, lists.W, lists.multi, lists.single, lists.wide, lists.counts);
 }
 
 // ---- the iterate ----------------------------------------------------------------
@@ -584,9 +632,8 @@ __host__ __device__ constexpr size_t tier_lds_bytes(int32_t R, int np) {
 //     share a wave while their slots fit its halves, so that half of the waves
 //     iterate, one per SIMD (a wave's SIMD is read from HW_ID; any placement
 //     still gives every pair one wave).
-// A problem that this kernel does not take gets its class for the others.
 template <int NP, int NW>
-__global__ void __launch_bounds__(NW * kWave) tier_solve_kernel(SkParams p, TierWs tw, int32_t* __restrict__ cls) {
+__global__ void __launch_bounds__(NW * kWave) tier_solve_kernel(SkParams p, TierWs tw, const int32_t* __restrict__ cls) {
   static_assert(NP == 1 || NP == NW, "a wave prepares one problem");
   extern __shared__ __attribute__((aligned(16))) char tier_lds[];
   __shared__ int32_t mine[NP], simd_of[NW];
@@ -598,35 +645,30 @@ __global__ void __launch_bounds__(NW * kWave) tier_solve_kernel(SkParams p, Tier
   int16_t* next = sl + R;
   double* prob = reinterpret_cast<double*>(tier_lds + tier_lds_slots(R));
   const int32_t stride = (int32_t)tier_lds_problem(R);
-  const bool tree_ok = tw.tree->ok != 0 && tw.tree->mismatch == 0;
+  if (tw.tree->ok == 0 || (NP == 1 && cls[pb0] != kTierClass)) return;  // uniform
 
-  if (tree_ok)
-    for (int32_t i = tid; i < R; i += NW * kWave) {
-      sl[i] = (int16_t)tw.slot[i];
-      next[i] = (int16_t)tw.next[i];
-    }
+  for (int32_t i = tid; i < R; i += NW * kWave) {
+    sl[i] = (int16_t)tw.slot[i];
+    next[i] = (int16_t)tw.next[i];
+  }
   // HW_ID bits 5:4 hold the SIMD of the wave
   const int simd = (int)__builtin_amdgcn_s_getreg((1 << 11) | (4 << 6) | 4);
   if (lane == 0) simd_of[wid] = simd;
 
-  // ---- marginals of a problem by one wave: validity, mass, supports -------------------
+  // ---- marginals of a problem by one wave ---------------------------------------------
   if (wid < NP) {
     const int64_t pb = pb0 + wid;
-    bool ok = false;
-    if (pb < p.B) {
+    const bool ok = pb < p.B && cls[pb] == kTierClass;
+    if (ok) {
       const float* a = p.a + pb * R;
       const float* bd = p.b + pb * R;
       double* s = prob + wid * stride;
       double* d = s + R;
       double sa = 0.0, sd = 0.0;
       int32_t nh = 0, nc = 0;
-      bool bad = false, other = false;
       for (int32_t base = 0; base < R; base += kWave) {
         const int32_t i = base + lane;
         const float ai = i < R ? a[i] : 0.f, bi = i < R ? bd[i] : 0.f;
-        bad |= !(ai >= 0.f && ai <= 3.402823466e38f) || !(bi >= 0.f && bi <= 3.402823466e38f);
-        other |= (ai > 0.f && bi > 0.f) || (ai > 0.f && !(ai >= kTierMassLo && ai <= kTierMassHi)) ||
-                 (bi > 0.f && !(bi >= kTierMassLo && bi <= kTierMassHi));
         nh += (int32_t)__popcll(__ballot(ai > 0.f));
         nc += (int32_t)__popcll(__ballot(bi > 0.f));
         sa += (double)ai;
@@ -638,34 +680,17 @@ __global__ void __launch_bounds__(NW * kWave) tier_solve_kernel(SkParams p, Tier
       }
       sa = wave_sum_d(sa);
       sd = wave_sum_d(sd);
-      double gamma = sd / fmax(sa, kEps0);
-      gamma = gamma < 1.0 ? gamma : 1.0;
-      const double surplus = sd / (gamma * sa);  // >= 1; its powers are the drift of the scalings
-      const bool any_bad = __ballot(bad) != 0;
-      ok = tree_ok && !any_bad && __ballot(other) == 0 && nh > 0 && nc > 0 &&
-           (double)p.iters * (surplus - 1.0) <= kTierDrift;
-      if (ok) {
-        for (int32_t i = lane; i < R; i += kWave) s[i] = gamma * s[i];
-        if (lane == 0 && p.status) {
-          // the status keeps telling problems whose support block no on-chip layout holds
-          const bool held = R <= kLdsMaxR || classify(nh, nc, p.flags) != 0 || wide_class(nh, nc, p.flags) != 0;
-          p.status[pb] = held ? 0u : TAOT_ST_STREAMED;
-        }
-        if (lane == 0) cls[pb] = kTierClass;
-      } else {
-        const bool invalid = any_bad || cost_bad_wave(p, pb);
-        int c = invalid ? 0 : classify(nh, nc, p.flags);
-        if (c == 0 && !invalid) c = wide_class(nh, nc, p.flags);
-        if (lane == 0) {
-          cls[pb] = c;
-          tw.left[0] = 1;
-        }
+      const double gamma = fmin(1.0, sd / fmax(sa, kEps0));
+      for (int32_t i = lane; i < R; i += kWave) s[i] = gamma * s[i];
+      if (lane == 0 && p.status) {
+        // the status keeps telling problems whose support block no on-chip layout holds
+        const bool held = R <= kLdsMaxR || classify(nh, nc, p.flags) != 0 || wide_class(nh, nc, p.flags) != 0;
+        p.status[pb] = held ? 0u : TAOT_ST_STREAMED;
       }
     }
     if (lane == 0) mine[wid] = ok ? 1 : 0;
   }
   __syncthreads();
-  if (!tree_ok || (NP == 1 && !mine[0])) return;  // uniform
 
   // ---- roles --------------------------------------------------------------------------
   const int nbits = tw.tree->nbits;
@@ -713,7 +738,10 @@ __global__ void __launch_bounds__(NW * kWave) tier_solve_kernel(SkParams p, Tier
       }
     }
   };
-  if (role >= 0) {
+  bool iterates = role >= 0;
+  if constexpr (NP > 1)  // (not for problems that other kernels solve)
+    if (iterates) iterates = (pair ? mine[2 * role] | mine[2 * role + 1] : mine[role]) != 0;
+  if (iterates) {
     const int q = pair ? 2 * role + (lane >= kWave / 2) : role;
     const double* s = prob + q * stride;
     double* kap = prob + q * stride + 2 * R;
@@ -736,7 +764,7 @@ __global__ void __launch_bounds__(NW * kWave) tier_solve_kernel(SkParams p, Tier
         default: break;
       }
     }
-  } else if (p.T) {
+  } else if (role < 0 && p.T) {
     for (int q = 0; q < NP; ++q)
       if (mine[q]) zero_rows(q, writer, writers);
   }
@@ -789,7 +817,7 @@ __global__ void __launch_bounds__(NW * kWave) tier_solve_kernel(SkParams p, Tier
 }
 
 template <int NP, int NW>
-taot_status launch_tier_solve(const SkParams& p, const TierWs& w, int32_t* cls, hipStream_t stream) {
+taot_status launch_tier_solve(const SkParams& p, const TierWs& w, const int32_t* cls, hipStream_t stream) {
   const size_t lds = tier_lds_bytes(p.R, NP);
   if (!allow_lds((const void*)tier_solve_kernel<NP, NW>, lds)) return TAOT_ERR_LAUNCH;
   hipLaunchKernelGGL((tier_solve_kernel<NP, NW>), dim3((unsigned)((p.B + NP - 1) / NP)), dim3(NW * kWave), lds, stream,
@@ -799,17 +827,13 @@ taot_status launch_tier_solve(const SkParams& p, const TierWs& w, int32_t* cls, 
 
 }  // namespace
 
-taot_status launch_tier(const SkParams& p, const TierWs& w, int32_t* cls, int32_t* cbad, hipStream_t stream) {
-  if (p.R <= kTierFusedR) {
-    hipLaunchKernelGGL(tier_prepass_kernel, dim3(1), dim3(kTreeThreads), 0, stream, w, p.C, p.R, p.eps, cbad);
-  } else {
-    const dim3 rows((unsigned)((p.R + kSkWaves - 1) / kSkWaves));
-    hipLaunchKernelGGL(tier_rows_kernel, rows, dim3(kSkThreads), 0, stream, w, p.C, p.R, cbad);
-    if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
-    hipLaunchKernelGGL(tier_tree_kernel, dim3(1), dim3(kTreeThreads), 0, stream, w, p.R, p.eps);
-    if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
-    hipLaunchKernelGGL(tier_check_kernel, dim3((rows.x + 3) / 4), dim3(kSkThreads), 0, stream, w, p.C, p.R);
-  }
+taot_status launch_tier(const SkParams& p, const TierWs& w, int32_t* cls, int32_t* cbad, const RegLists& lists,
+                        hipStream_t stream) {
+  const int32_t row_blocks = (p.R + kSkWaves - 1) / kSkWaves;
+  const unsigned grid = (unsigned)row_blocks + (unsigned)(((int64_t)p.B + kSkWaves - 1) / kSkWaves);
+  hipLaunchKernelGGL(tier_rows_kernel, dim3(grid), dim3(kSkThreads), 0, stream, p, w, row_blocks, cls);
+  if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
+  hipLaunchKernelGGL(tier_tree_kernel, dim3(1), dim3(kTreeThreads), 0, stream, p, w, cls, cbad, lists);
   if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   // the shape: see the kernel; eight problems to a group from where one
   // iterating wave per problem would put two on a SIMD

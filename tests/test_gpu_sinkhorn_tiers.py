@@ -151,6 +151,51 @@ def test_other_costs_are_left(case, gpu):
     _check(a, b, C, eps, 60, tier=False)
 
 
+def _near_tree(rng, R, levels, changed):
+    """Nested random groups of shuffled ranks; then `changed` entries at other tiers, half of them on one side only."""
+    C = np.full((R, R), float(levels), np.float32)
+    key = np.zeros(R, int)
+    for l in range(levels - 1, 0, -1):
+        key = key * 3 + rng.integers(0, 3, size=R)
+        C[key[:, None] == key[None, :]] = l
+    for _ in range(changed):
+        i, j = rng.choice(R, 2, replace=False)
+        C[i, j] = rng.integers(1, levels + 1)
+        if rng.random() < 0.5:
+            C[j, i] = C[i, j]
+    np.fill_diagonal(C, 0.0)
+    return C
+
+
+@pytest.mark.parametrize("R", [3, 5, 9, 40, 70, 300, 1100])
+def test_near_trees(R, gpu):
+    """Trees and matrices one or two entries away from one, which only a look
+    at every entry tells apart: all agree with the oracle."""
+    rng = np.random.default_rng(R)
+    for k in range(24 if R < 100 else 6):
+        levels = int(rng.integers(2, 5))
+        C = _near_tree(rng, R, levels, k % 3)
+        a, b = _marginals(rng, R, 2)
+        _check(a, b, C, 0.1, 12, tier=False)
+
+
+def test_problems_that_are_left_beside_solved_ones(gpu):
+    """In one call over a tree: every third problem has a rank on both sides;
+    the register, wide and streamed kernels then run on the lists that the
+    prepass leaves, in batches of one and of eight problems to a group."""
+    rng = np.random.default_rng(12)
+    for R, B in ((64, 9), (130, 1030), (300, 9), (1100, 5)):
+        C = _tree_cost(R, (8, 64), (1.0, 3.0, 8.0))
+        a, b = _marginals(rng, R, B)
+        for p in range(0, B, 3):
+            b[p, int(a[p].argmax())] = 3.0
+        at = list(range(0, B, 1 if B < 100 else 41))
+        T = _run(a, b, C, 0.2, 25)[0]
+        a64, b64 = a[at].astype(np.float64), b[at].astype(np.float64)
+        ref = O.sinkhorn(a64, b64, C.astype(np.float64), 0.2, 25)
+        sinkhorn_check(T[at], ref.T, a64, b64)
+
+
 def test_marginals_that_are_left(gpu):
     """Overlapping supports, more demand than supply (the scalings drift by
     the ratio in every iteration), tiny and huge marginals."""
