@@ -564,6 +564,7 @@ struct LdsSmall {
   static constexpr int kNEC = 128;   // candidate experts (spill > 0) in LDS
   static constexpr int kWavesPerEU = 8;  // large batches: eight problems per compute unit (20 KB of LDS each at R = 256, K = 2)
   static constexpr int kG = 2;       // bid groups per lane that the auction keeps in registers
+  static constexpr int kAW = 1;      // waves of the auction while its list is long
 };
 struct LdsTiny {
   static constexpr int kT = 64;      // one wave per problem: its barriers cost next to nothing
@@ -575,6 +576,7 @@ struct LdsTiny {
   static constexpr int kNEC = 128;
   static constexpr int kWavesPerEU = 8;
   static constexpr int kG = 1;
+  static constexpr int kAW = 1;
 };
 struct LdsLarge {
   static constexpr int kT = 1024;
@@ -585,7 +587,8 @@ struct LdsLarge {
   static constexpr int kMaxS = 4096;
   static constexpr int kNEC = 1024;
   static constexpr int kWavesPerEU = 1;  // one problem per compute unit in any case
-  static constexpr int kG = 4;
+  static constexpr int kG = 3;
+  static constexpr int kAW = 8;
 };
 // The count window's rebuild takes rank r on thread r (wave w builds word w).
 static_assert(LdsSmall::kT == LdsSmall::kTW * kWave && LdsTiny::kT == LdsTiny::kTW * kWave &&
@@ -972,7 +975,29 @@ __device__ __forceinline__ int set_word(int32_t row, int w) {
   return w ^ (row & (TW - 1));
 }
 
-// The rounds of the auction, on one wave; returns how many ran.
+// Where the rounds of an auction stand: the next round, the list's length, the
+// base count, the ranks at it, the epoch's parity, the base count's price,
+// whether the planes of the full counts are kept, whether no bid was left.
+struct AuctionRun {
+  int64_t t;
+  int32_t nw, base, base_left;
+  uint32_t epoch;
+  double P0;
+  bool planes_on, done;
+};
+// What the waves of one auction share, in LDS: two counts of live groups (by the
+// round's parity), ranks left at the base count, planes_on, the list's length.
+constexpr int kShLive = 0, kShLeft = 2, kShPlanes = 3, kShList = 4, kShWords = 5;
+// Up to this many groups one wave goes on alone.
+constexpr int32_t kAuctionAlone = 64;
+
+// Barrier for LDS alone: loads and stores of device memory stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The rounds of the auction from `run` on: on one wave to the end, or on NW
+// waves until one wave can go on alone.
 //
 // Every bid names a rank, which then serves its best bidder with a positive
 // amount; so every group with an open slot and a valid rank bids again in
@@ -987,6 +1012,14 @@ __device__ __forceinline__ int set_word(int32_t row, int w) {
 // so a round costs its chain of latencies.  One wave runs it without a barrier,
 // as the LDS operations of a wave stay in order; lists of up to 64 kG groups
 // stay in registers, kG to a lane, longer ones are walked 64 at a time.
+//
+// Above R = 256 a list can hold a thousand groups, and a wave's round over it
+// grows with it.  There kAW waves hold the list in registers, with a barrier
+// behind X and one behind Y, until kAuctionAlone groups are left.  64 x R = 1024,
+// K = 2, lists of about 410: 24.0 ms a call on one wave, 20.9 with eight waves
+// down to 256 groups, 16.2 down to 64; 16 problems of R = 1024 with 950 groups
+// each: 21.5 ms on one wave, 17.0 and 13.8.  Four waves with five groups a lane:
+// 15.0; sixteen with two: 13.8.
 //
 // Incremental bids.  Within an epoch (while the base count stays) a group keeps
 // its first tier ts that holds a valid rank, the fewest services lev (above the
@@ -1013,24 +1046,28 @@ __device__ __forceinline__ int set_word(int32_t row, int w) {
 // and the base moves at most once per round).  Between the two steps of a round
 // over a longer list the spare bits hold the bit of the bid's rank in word w:
 // two bits in the entry (26-27), four in the state (12-15).
-template <class CF>
-__device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const int16_t* gnext, int32_t* np,
-                                                  int32_t* Xb, int32_t R, int32_t S, int32_t nw, double step,
-                                                  int64_t tmax) {
-  constexpr int TW = CF::kTW, G = CF::kG;
+template <class CF, int NW>
+__device__ __forceinline__ void auction_rounds(const LdsState<CF>& L, AuctionRun& run, int32_t* sh,
+                                               const int16_t* gnext, int32_t* np, int32_t* Xb, int32_t R, int32_t S,
+                                               double step, int64_t tmax) {
+  constexpr int TW = CF::kTW;
+  constexpr int G = NW == 1 && CF::kAW > 1 ? kAuctionAlone / kWave : CF::kG;  // groups of a lane
   constexpr int32_t kSlotMask = (1 << kItemSlotBits) - 1, kExpMask = (1 << kItemExpertBits) - 1;
   constexpr int32_t kItemBits = 26, kItemMask = (1 << kItemBits) - 1;
   constexpr int32_t kStructMask = (1 << (kItemBits - kItemSlotBits - kItemExpertBits)) - 1;
+  // a matched slot uses up its rank's spare or its expert's spill: no more slots than ranks and slot experts
+  static_assert(NW == 1 || NW * kWave * G >= CF::kTW * kWave + CF::kDC, "the waves hold every list");
   constexpr uint32_t kHas = 1u << 10, kStateMask = (1u << 12) - 1u;
   static_assert(TW <= 16 && kTierMax <= 4 && kRelMax <= 15 && CF::kSC <= kStructMask + 1, "entry and state fields");
   const int lane = threadIdx.x & (kWave - 1);
   const bool track = step > 0.0;  // counts order the prices; with step 0 all prices stay 0
   uint32_t* rk = L.rkey;
   const int32_t* nmax = L.dexp;
-  double P0 = 0.0;                // price of the base count
-  int32_t base = 0, base_left = R;
-  uint32_t epoch = 0;             // parity
-  bool planes_on = false;         // the planes of the full counts are kept from their first use on
+  const int wid = NW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : 0;
+  double P0 = run.P0;             // price of the base count
+  int32_t base = run.base, base_left = run.base_left, nw = run.nw;
+  uint32_t epoch = run.epoch;     // parity
+  bool planes_on = run.planes_on; // the planes of the full counts are kept from their first use on
 
   // word w of tier e = structure * kTierMax + tier, and of expert d's valid
   // ranks (rows of TW words, rotated so that the same word of different rows
@@ -1164,6 +1201,8 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
         }
       }
       planes_on = true;
+      if constexpr (NW > 1)
+        if (lane == 0) sh[kShPlanes] = 1;  // (another wave that makes them now writes the same)
       if (need) x = search(it, b.state, stuck);
     }
     b = x;
@@ -1205,18 +1244,19 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
     for (int32_t r = lane; r < R; r += kWave) mn = min(mn, L.cnt[r]);
     base = __builtin_amdgcn_readfirstlane(-wave_max_i32(-mn));
     base_left = 0;
+    const bool writes = lane == 0 && wid == 0;
     for (int w = 0; w < TW; ++w) {
       const int32_t r = w * kWave + lane;
       const int32_t kr = r < R ? min(L.cnt[r] - base, kRelMax) : -1;
       const uint64_t m0 = __ballot(kr == 0), m1 = __ballot(kr == 1);
-      if (lane == 0) {
+      if (writes) {
         L.lvl[w] = m0;
         L.lvl[TW + w] = m1;
       }
 #pragma unroll
       for (int j = 0; j < kRelPlanes; ++j) {
         const uint64_t m = __ballot(kr > 0 && ((kr >> j) & 1));
-        if (lane == 0) L.rel[j * TW + w] = m;
+        if (writes) L.rel[j * TW + w] = m;
       }
       // every rank at the new base has the same price
       if (m0 != 0ull) P0 = L.price[w * kWave + (int)__builtin_ctzll(m0)];
@@ -1225,7 +1265,8 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
     epoch ^= 1u;
   };
 
-  int64_t t = 1;
+  int64_t t = run.t;
+  if constexpr (CF::kAW == 1) {
   // ---- lists longer than a wave: entries and states in LDS -----------------------------
   int32_t active = nw;
   for (; t <= tmax && nw > G * kWave; ++t) {
@@ -1261,7 +1302,11 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
       }
       bids += (int32_t)__popcll(__ballot(b.r >= 0));
     }
-    if (bids == 0) return t - 1;  // no bid: the state is final
+    if (bids == 0) {  // no bid: the state is final
+      run.t = t;
+      run.done = true;
+      return;
+    }
     active = bids;
     // Y: the winners of all entries, gathered a lane each, then their transfers
     int32_t wq = -1, have_n = 0;
@@ -1331,15 +1376,17 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
       nw = kept;
     }
   }
+  }
   // ---- up to G groups per lane, in registers ------------------------------------------------
-  while (t <= tmax) {
-    const int32_t sets = (nw + kWave - 1) / kWave;  // in use; the list closes up when one less will do
+  bool done = false;
+  while (t <= tmax && !done && (NW == 1 || nw > kAuctionAlone)) {
+    const int32_t sets = (nw + NW * kWave - 1) / (NW * kWave);  // in use; the list closes up when one less will do
     int32_t it[G], a[G], most[G];  // entry, tokens planned, the most a rank can hold
     int32_t pr[G], pv[G];          // a transfer in flight: its rank and what the rank held
     Bid b[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const int32_t q = g * kWave + lane;
+      const int32_t q = (g * NW + wid) * kWave + lane;
       it[g] = q < nw ? L.work[q] : -1;
       b[g] = Bid{-1, 0, 0u, 0ull};
       a[g] = most[g] = pv[g] = 0;
@@ -1356,7 +1403,6 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
       a[g] -= pv[g];
       pr[g] = -1;
     };
-    bool done = false;
     for (; t <= tmax; ++t) {
       int32_t r[G];
 #pragma unroll
@@ -1390,10 +1436,6 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
         }
         live += (int32_t)__popcll(__ballot(it[g] >= 0));
       }
-      if (live == 0) {  // no bid: the state is final
-        done = true;
-        break;
-      }
       uint32_t key[G], k[G];
       int32_t c0[G];
       double price[G];
@@ -1402,6 +1444,22 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
         key[g] = ((uint32_t)b[g].v << 16) | (uint32_t)(0xFFFF - (it[g] & kSlotMask));
         if (g < sets && it[g] >= 0) atomicMax(&rk[r[g]], key[g]);
       }
+      if constexpr (NW > 1) {
+        int32_t* const count = sh + kShLive + (int)(t & 1);
+        if (lane == 0) atomicAdd(count, live);
+        lds_barrier();
+        live = __builtin_amdgcn_readfirstlane(*count);
+        planes_on = __builtin_amdgcn_readfirstlane(sh[kShPlanes]) != 0;
+        if (threadIdx.x == 0) {  // (read last before the barrier above)
+          sh[kShLive + (int)((t + 1) & 1)] = 0;
+          sh[kShList] = 0;
+        }
+      }
+      if (live == 0) {  // no bid: the state is final
+        done = true;
+        break;
+      }
+      int32_t gone = 0;  // ranks that leave the base count
 #pragma unroll
       for (int g = 0; g < G; ++g) {  // (the rank's count and price come with its key)
         if (g >= sets) continue;
@@ -1422,7 +1480,7 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
           pr[g] = r[g];
           left_base = serve(r[g], c0[g], price[g]);
         }
-        base_left -= (int32_t)__popcll(__ballot(left_base));
+        gone += (int32_t)__popcll(__ballot(left_base));
         const bool wait = won && a[g] <= most[g];  // the slot may fill
         if (won && !wait) drained(expert(it[g]), r[g]);
         if (__ballot(wait) != 0) {
@@ -1430,6 +1488,7 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
             const int32_t d = expert(it[g]), s = it[g] & kSlotMask, have = pv[g];
             if (have <= a[g]) drained(d, r[g]);
             else np[(int64_t)d * R + r[g]] = have - a[g];
+            if constexpr (NW > 1) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // another wave may read it
             pv[g] = have < a[g] ? have : a[g];
             book(g);
             if (a[g] == 0) {
@@ -1441,12 +1500,25 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
           }
         }
       }
-      if (track && base_left == 0) rebase();
-      if (sets > 1 && live <= kWave * (sets - 1)) {
+      if constexpr (NW > 1) {
+        if (lane == 0 && gone) atomicSub(&sh[kShLeft], gone);
+        lds_barrier();
+        if (track && __builtin_amdgcn_readfirstlane(sh[kShLeft]) == 0) {
+          lds_barrier();  // every wave has read the count
+          rebase();
+          if (threadIdx.x == 0) sh[kShLeft] = base_left;
+          lds_barrier();
+        }
+      } else {
+        base_left -= gone;
+        if (track && base_left == 0) rebase();
+      }
+      if ((sets > 1 && live <= NW * kWave * (sets - 1)) || (NW > 1 && live <= kAuctionAlone)) {
         ++t;
         break;
       }
     }
+    if (done) break;
     int32_t kept = 0;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -1455,6 +1527,11 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
         L.amt[it[g] & kSlotMask] = a[g];
       }
       const uint64_t m = __ballot(it[g] >= 0);
+      if constexpr (NW > 1) {
+        int32_t at = 0;
+        if (lane == 0 && m) at = atomicAdd(&sh[kShList], (int32_t)__popcll(m));
+        kept = __builtin_amdgcn_readfirstlane(at);
+      }
       const int32_t to = kept + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
       if (it[g] >= 0) {
         L.work[to] = it[g];
@@ -1462,10 +1539,14 @@ __device__ __forceinline__ int64_t auction_rounds(const LdsState<CF>& L, const i
       }
       kept += (int32_t)__popcll(m);
     }
-    if (done) break;
     nw = kept;
+    if constexpr (NW > 1) {
+      lds_barrier();
+      nw = __builtin_amdgcn_readfirstlane(sh[kShList]);
+      base_left = __builtin_amdgcn_readfirstlane(sh[kShLeft]);
+    }
   }
-  return t - 1;
+  run = AuctionRun{t, nw, base, base_left, epoch, P0, planes_on, done};
 }
 
 // LDS of the auction alone.
@@ -1531,13 +1612,20 @@ __device__ __forceinline__ void auction_start(const LdsState<CF>& L, const LdsPa
 // Rounds and results of problem b on one wave.
 template <class CF>
 __device__ __forceinline__ void auction_problem(const LdsState<CF>& L, const LdsParams& wp, int64_t b, int32_t nw,
-                                                int32_t used2) {
+                                                int32_t used2, int32_t* sh) {
   const SchParams& p = wp.s;
   const int32_t R = p.R, S = p.R * p.K;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t tmax = p.t_max > 0 ? p.t_max : (int64_t)S * (R + 1);
-  const int64_t rounds = auction_rounds<CF>(L, L.slot_ec, wp.nprime + b * (int64_t)CF::kDC * R,
-                                            p.X + b * (int64_t)R * S, R, S, nw, p.price_step, tmax);
+  int32_t* const np = wp.nprime + b * (int64_t)CF::kDC * R;
+  int32_t* const Xb = p.X + b * (int64_t)R * S;
+  AuctionRun run{1, nw, 0, R, 0u, 0.0, false, false};
+  if constexpr (CF::kAW > 1) {
+    if (nw > kAuctionAlone) auction_rounds<CF, CF::kAW>(L, run, sh, L.slot_ec, np, Xb, R, S, p.price_step, tmax);
+    if (threadIdx.x >= kWave) return;
+  }
+  if (!run.done) auction_rounds<CF, 1>(L, run, nullptr, L.slot_ec, np, Xb, R, S, p.price_step, tmax);
+  const int64_t rounds = run.t - 1;
   int64_t left = 0;  // (a slot without an expert plans 0 tokens)
   for (int32_t s = lane; s < S; s += kWave) left += L.amt[s];
   const int64_t tot = wave_sum_i64(left);
@@ -1549,33 +1637,35 @@ __device__ __forceinline__ void auction_problem(const LdsState<CF>& L, const Lds
   }
 }
 
-// The auction of one problem per one-wave workgroup, for the configurations
+// The auction of one problem per workgroup of kAW waves, for the configurations
 // whose matching kernel has several waves: it needs few waves but many
 // registers, and other workgroups' matching can take the compute unit's rest.
 template <class CF>
-__global__ void __launch_bounds__(kWave) auction_kernel(LdsParams wp) {
-  constexpr int TW = CF::kTW;
+__global__ void __launch_bounds__(CF::kAW * kWave) auction_kernel(LdsParams wp) {
+  constexpr int TW = CF::kTW, NT = CF::kAW * kWave;
+  __shared__ int32_t sh[kShWords];
   extern __shared__ __attribute__((aligned(16))) char lds_dyn[];
   const int64_t b = blockIdx.x;
   const int4 h = wp.h.hdr[b];
   if (h.x < 0) return;
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x;
   const int32_t R = wp.s.R, S = wp.s.R * wp.s.K;
   const LdsState<CF> L = carve_auction<CF>(lds_dyn, R, wp.s.K);
-  auction_start<CF, kWave>(L, wp, R);
-  for (int32_t q = lane; q < S; q += kWave) {
+  auction_start<CF, NT>(L, wp, R);
+  for (int32_t q = tid; q < S; q += NT) {
     L.amt[q] = wp.h.amt[b * S + q];
     L.slot_ec[q] = wp.h.gnext[b * S + q];
     L.sstate[q] = 0;  // no bid yet
   }
-  for (int32_t q = lane; q < h.x; q += kWave) L.work[q] = wp.h.work[b * S + q];
-  for (int32_t q = lane; q < h.z; q += kWave) {
+  for (int32_t q = tid; q < h.x; q += NT) L.work[q] = wp.h.work[b * S + q];
+  for (int32_t q = tid; q < h.z; q += NT) {
     L.dexp[q] = wp.h.nmax[b * CF::kDC + q];
     if constexpr (TW > 4) L.vwords[q] = wp.h.vwords[b * CF::kDC + q];
   }
-  for (int32_t q = lane; q < h.z * TW; q += kWave) L.vmask[q] = wp.h.vmask[b * CF::kDC * TW + q];
+  for (int32_t q = tid; q < h.z * TW; q += NT) L.vmask[q] = wp.h.vmask[b * CF::kDC * TW + q];
+  if (tid < kShWords) sh[tid] = tid == kShLeft ? R : 0;
   __syncthreads();
-  auction_problem<CF>(L, wp, b, __builtin_amdgcn_readfirstlane(h.x), h.y);
+  auction_problem<CF>(L, wp, b, __builtin_amdgcn_readfirstlane(h.x), h.y, sh);
 }
 
 // Validation, matching and the auction's lists of one problem per workgroup of
@@ -1992,7 +2082,7 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
     for (int32_t s = tid; s < S; s += NT) L.sstate[s] = 0;  // no bid yet
     auction_start<CF, NT>(L, wp, R);
     __syncthreads();
-    auction_problem<CF>(L, wp, b, sh_nw, used2);
+    auction_problem<CF>(L, wp, b, sh_nw, used2, nullptr);
   } else {
     for (int32_t q = tid; q < S; q += NT) {
       wp.h.amt[b * S + q] = L.amt[q];
@@ -2115,7 +2205,7 @@ taot_status launch_lds_path(const SchParams& p, const SchWs& w, int32_t B, int32
   if (st != TAOT_OK) return st;
   if constexpr (CF::kT > kWave) {
     if (!allow_lds((const void*)auction_kernel<CF>, alds)) return TAOT_ERR_LAUNCH;
-    hipLaunchKernelGGL(auction_kernel<CF>, dim3((unsigned)B), dim3(kWave), alds, stream, wp);
+    hipLaunchKernelGGL(auction_kernel<CF>, dim3((unsigned)B), dim3(CF::kAW * kWave), alds, stream, wp);
     if (hipGetLastError() != hipSuccess) return TAOT_ERR_LAUNCH;
   }
   launched = true;

@@ -1,6 +1,8 @@
 """GPU parity of taot_round_schedule (Phase 2 + Phase 3) with the oracle:
 bit-exact when both sides consume the same fp32 plan (the oracle's plan cast
 to fp32)."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -229,6 +231,40 @@ def test_bid_groups(t_max, gpu):
     open_ = (se >= 0) & (sa > 0)
     keys = {(b, h % 3, e) for b in range(B) for h, e in zip(np.nonzero(open_[b])[0] // K, se[b][open_[b]])}
     assert open_.sum() >= 4 * len(keys)
+
+
+def _long_lists(R, K, hot, tokens, idle, seed=0):
+    """Every rank but `hot` of them takes tokens of one of `hot` experts, so
+    that almost every rank's slot is a bid group of its own; `idle` ranks hold
+    no token of those experts."""
+    rng = np.random.default_rng(seed)
+    E = 2 * R
+    home = (np.arange(E) // 2).astype(np.int32)
+    at = np.sort(rng.permutation(R)[:hot])
+    spare, excess, spill = np.zeros((1, R), np.int64), np.zeros((1, R), np.int64), np.zeros((1, E), np.int64)
+    cold = np.setdiff1d(np.arange(R), at)
+    spare[0, cold] = rng.integers(tokens // 2, tokens * 3 // 2, size=cold.size)
+    each = int(spare.sum()) // hot
+    excess[0, at], spill[0, 2 * at] = each, each
+    n = rng.poisson(0.2, (1, R, E)).astype(np.int32)
+    n[0, :, 2 * at] = rng.poisson(1.3 * each / R, (hot, R))
+    n[0, :idle, 2 * at] = 0
+    return SimpleNamespace(n=n, spill=spill, spare=spare, excess=excess, alpha=np.array([tokens / 5.0])), home
+
+
+@pytest.mark.parametrize("R,K,hot", [(300, 2, 30), (640, 2, 71), (1024, 1, 128), (1024, 4, 120)])
+@pytest.mark.parametrize("eta,t_max,idle", [(2.0 ** -6, 0, 0), (2.0 ** -6, 0, 3), (0.0, 0, 0), (2.0 ** -6, 7, 0)])
+def test_long_lists(R, K, hot, eta, t_max, idle, gpu):
+    """Lists of more groups than one wave holds: the auction's waves share the
+    rounds until few are left (R K up to the layout's 4096 slots, 128 slot
+    experts).  Ranks that never serve keep the base count at 0 while others
+    serve 15 times and more (the planes of the full counts), step 0 keeps no
+    counts, and a round cap ends the shared rounds."""
+    print(f"[schedule parity] long lists R={R} K={K} eta={eta} t_max={t_max} idle={idle}", flush=True)
+    L, home = _long_lists(R, K, hot, 40, idle, seed=R + K)
+    Bp, Ba = O.topology_pref(W.cost_matrix_for(R, ("fat_tree", 1.0, 4.0, 16.0, 64)))
+    se, *_ = _compare(L, home, np.zeros((1, R, R), np.float32), Bp, Ba, K, t_max=t_max, eta=eta, label=f"R{R} K{K}")
+    assert (se >= 0).sum() > 256
 
 
 def test_workload4_problem(gpu):
