@@ -513,11 +513,14 @@ __global__ void __launch_bounds__(kSchThreads) schedule_kernel(SchParams p) {
 
 // ===========================================================================
 // LDS-resident path.  Same arithmetic and order as schedule_kernel, with one
-// workgroup per problem and all of its state in LDS and registers.  Two size
-// configurations: 256 threads for R <= 256 and R*K <= 1024 (several problems
-// per compute unit), 1024 threads for R <= 1024 and R*K <= 4096 (up to
-// ~155 KB of LDS, one problem per compute unit).  Both need bonuses (Bauct
-// columns) that take few distinct values, as topology costs do.
+// workgroup per problem and all of its state in LDS and registers.  Three size
+// configurations: one wave for R <= 64 and R*K <= 256, 256 threads for R <= 256
+// and R*K <= 1024 (several problems per compute unit in both), 1024 threads for
+// R <= 1024 and R*K <= 4096.  One wave runs matching and auction in one kernel;
+// the others run the matching (36 to 100 KiB of LDS at R > 256) and then the
+// auction in a kernel of its own (103 to 156 KiB there: one problem per compute
+// unit).  All need bonuses (Bauct columns) that take few distinct values, as
+// topology costs do.
 //
 // Phase-3 bids by tiers.  The ranks of host column h split into tiers of equal
 // bonus (descending).  With prices that start at 0 and rise by a fixed step on
@@ -562,7 +565,7 @@ struct LdsSmall {
   static constexpr int kPL = 11;     // count bit-planes: counts <= R*K <= 1024
   static constexpr int kMaxS = 1024; // R*K
   static constexpr int kNEC = 128;   // candidate experts (spill > 0) in LDS
-  static constexpr int kWavesPerEU = 8;  // large batches: eight problems per compute unit (20 KB of LDS each at R = 256, K = 2)
+  static constexpr int kWavesPerEU = 8;  // large batches: eight problems per compute unit (17 KB of LDS each at R = 256, K = 2)
   static constexpr int kG = 2;       // bid groups per lane that the auction keeps in registers
   static constexpr int kAW = 1;      // waves of the auction while its list is long
 };
@@ -586,7 +589,7 @@ struct LdsLarge {
   static constexpr int kPL = 13;     // counts <= R*K <= 4096
   static constexpr int kMaxS = 4096;
   static constexpr int kNEC = 1024;
-  static constexpr int kWavesPerEU = 1;  // one problem per compute unit in any case
+  static constexpr int kWavesPerEU = 1;  // the auction, one problem per compute unit, is the longer part by far
   static constexpr int kG = 3;
   static constexpr int kAW = 8;
 };
@@ -852,7 +855,7 @@ struct LdsState {
 
 template <class CF>
 __host__ __device__ inline LdsState<CF> carve_lds(char* base, int32_t R, int32_t K, int32_t NEC) {
-  LdsState<CF> w;
+  LdsState<CF> w{};
   const size_t S1 = R * K > 0 ? (size_t)R * K : 1, R_ = (size_t)R, N_ = (size_t)NEC;
   constexpr size_t TW = CF::kTW, SC = CF::kSC, DC = CF::kDC;
   size_t off = 0;
@@ -872,7 +875,6 @@ __host__ __device__ inline LdsState<CF> carve_lds(char* base, int32_t R, int32_t
   w.qbest = (int32_t*)take(4 * R_);
   const size_t end2 = off;
   off = split;
-  w.price = (double*)take(8 * R_); w.rkey = (uint32_t*)take(4 * R_);
   w.work = (int32_t*)take(4 * S1);
   // the list entries' bid states, by list position, over the candidates' slot
   // expert indices (read last when the list's items are built)
@@ -881,13 +883,16 @@ __host__ __device__ inline LdsState<CF> carve_lds(char* base, int32_t R, int32_t
   // the word lists guide the per-word search of sets wider than 4 words only
   w.vmask = (uint64_t*)take(8 * DC * TW); w.vwords = (uint32_t*)take(TW > 4 ? 4 * DC : 0);
   w.dexp = (int32_t*)take(4 * DC);
-  w.cnt = (int32_t*)take(4 * R_); w.planes = (uint64_t*)take(8 * CF::kPL * TW);
-  w.lvl = (uint64_t*)take(2 * 8 * TW);
-  w.rel = (uint64_t*)take(8 * kRelPlanes * TW);
-  w.cn = (int8_t*)take(SC);
-  w.cv = (double*)take(8 * SC * kTierMax); w.cvr = (int32_t*)take(4 * SC * kTierMax);
-  w.cw = (uint32_t*)take(4 * SC * kTierMax);
-  w.cm = (uint64_t*)take(8 * SC * kTierMax * TW);
+  if constexpr (CF::kT == kWave) {  // the auction follows in the same kernel
+    w.price = (double*)take(8 * R_); w.rkey = (uint32_t*)take(4 * R_);
+    w.cnt = (int32_t*)take(4 * R_); w.planes = (uint64_t*)take(8 * CF::kPL * TW);
+    w.lvl = (uint64_t*)take(2 * 8 * TW);
+    w.rel = (uint64_t*)take(8 * kRelPlanes * TW);
+    w.cn = (int8_t*)take(SC);
+    w.cv = (double*)take(8 * SC * kTierMax); w.cvr = (int32_t*)take(4 * SC * kTierMax);
+    w.cw = (uint32_t*)take(4 * SC * kTierMax);
+    w.cm = (uint64_t*)take(8 * SC * kTierMax * TW);
+  }
   w.bytes = end2 > off ? end2 : off;
   return w;
 }
