@@ -118,7 +118,7 @@ home_csr_kernel(const int32_t* __restrict__ home, int32_t B, int32_t R, int32_t 
 // (two register sets, a and b, take turns).  The first batch is issued before
 // the counters are cleared.  A row may start and end off a 16-byte boundary
 // (N % 4 != 0): the ids before the first and behind the last go one by one (7 x
-// 24 rows of 73734 ids: 25 us a call; 92 when such rows were read id by id).
+// 24 rows of 73734 ids: 27 us a call; 92 when such rows were read id by id).
 template <bool PACK16>
 __global__ void __launch_bounds__(kHistThreads)
 histogram_kernel(const int32_t* __restrict__ ids, int64_t N, int32_t R, int32_t E, int32_t copies, bool half,
@@ -244,7 +244,7 @@ histogram_kernel(const int32_t* __restrict__ ids, int64_t N, int32_t R, int32_t 
 // x_e = sum_r n_re for a block of kColExperts experts of one problem: lane l
 // of every wave sums experts 4l .. 4l+3 of the block (one 16-byte load per
 // row when rows are 16-byte aligned, else four 4-byte loads), wave w rows
-// w, w + 4, ...; the waves' partial sums meet in LDS.  Integer sums: exact in
+// w, w + NT / 64, ...; the waves' partial sums meet in LDS.  Integer sums: exact in
 // any order.
 //
 // HALF: the histogram left the block's counts of each row as 16-bit pairs

@@ -1790,8 +1790,10 @@ __global__ void __launch_bounds__(CF::kT, WPE) schedule_lds_kernel(LdsParams wp)
   // index, it is the best of all, and a rank whose list holds all its
   // candidates never scans again.  The register-capped build has no room for
   // lists and enough problems in flight to hide a scan's loads (1952 x R = 256:
-  // 3.14 ms a call, 3.3 to 3.9 with lists of 1 to 4); elsewhere the scans are
-  // the matching's time (58 x R = 64: 345 -> 317 us a call).
+  // 3.14 ms a call, 3.3 to 3.9 with lists of 1 to 4; one-wave problems, 3000 x R =
+  // 64: 465 us, 541 and 548 with lists of 2 and 4; 3000 x R = 32, K = 4: 230, 265
+  // and 273); elsewhere the scans are the matching's time (58 x R = 64: 345 -> 317
+  // us a call).
   constexpr int kBestOf = WPE > 1 ? 0 : 4, kList = kBestOf > 0 ? kBestOf : 1;
   int32_t used2 = 0;
   const int32_t rc = tid;

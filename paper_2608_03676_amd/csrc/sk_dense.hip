@@ -26,8 +26,6 @@
 //       column in a fixed order and sets v_j.
 // All reductions run in a fixed order, so results do not depend on
 // scheduling.
-
-
 #include "sk_common.h"
 
 namespace taot {
