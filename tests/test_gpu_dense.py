@@ -53,7 +53,8 @@ def test_dense_workloads(cfg, problems, gpu):
 def test_dense_ragged_shapes(R, per_problem, gpu):
     """R across one and several row blocks of 64, partial waves and phases,
     both row kernels (R % 4 != 0 takes the phased one: 8 columns per thread
-    and 4-row phases at R = 1027) and both column-update widths (R > 1024);
+    and 4-row phases at R = 1027), column updates over one and several tiles
+    of rows (R > 256);
     random supports with zeros on both sides; costs shared or one matrix per
     problem."""
     rng = np.random.default_rng(R * 7 + per_problem)

@@ -282,9 +282,9 @@ def test_workload4_problem(gpu):
 def test_large_batches(R, K, gpu):
     """Batches of more than six problems per compute unit take the
     register-capped builds of the LDS kernels (eight problems per compute
-    unit): the one-wave configuration up to R = 64, the 256-thread one
-    above, which packs its auction list (one slot per thread at R K <= 256,
-    two above); every problem bit-exact with the oracle."""
+    unit; no candidate lists in the matching): the one-wave configuration up
+    to R = 64, the 256-thread one with the auction in a kernel of its own
+    above; every problem bit-exact with the oracle."""
     B = 1600 if R <= 64 else 1700
     print(f"[schedule parity] large batch B={B} R={R} K={K}", flush=True)
     _, L, home, T32, Bp, Ba = _instance(500 + R, R, E=2 * R, N=120, B=B)

@@ -8,7 +8,7 @@ import torch
 import oracle as O
 import paper_2608_03676_amd as taot
 import workloads as W
-from helpers import oracle_inputs, potentials_check, sinkhorn_check
+from helpers import off_tree, oracle_inputs, potentials_check, sinkhorn_check
 
 pytestmark = pytest.mark.gpu
 
@@ -37,14 +37,15 @@ def _check_against_oracle(a32, b32, C32, eps, iters, flags=0):
 
 @pytest.mark.parametrize("cfg,problems", [(0, [0]), (1, list(range(58))), (2, list(range(0, 384, 24))),
                                           (3, [0, 1, 2, 977, 1951])])
-@pytest.mark.parametrize("flags", [0, taot.SK_NO_REGISTER])
-def test_workloads(cfg, problems, flags, gpu):
-    """Default flags take the register-resident path at these sizes;
-    SK_NO_REGISTER takes the LDS-resident one."""
+@pytest.mark.parametrize("flags,tree", [(0, True), (0, False), (taot.SK_NO_REGISTER, True)])
+def test_workloads(cfg, problems, flags, tree, gpu):
+    """Default flags take the tier path for the workloads' costs and the
+    register-resident path for costs that are no tree; SK_NO_REGISTER takes
+    the LDS-resident one."""
     w = W.WORKLOADS[cfg]
-    print(f"[sinkhorn parity] workload {cfg} problems {problems} flags {flags}", flush=True)
+    print(f"[sinkhorn parity] workload {cfg} problems {problems} flags {flags} tree {tree}", flush=True)
     _, L = oracle_inputs(w, problems)
-    C = W.cost_matrix(w)
+    C = W.cost_matrix(w) if tree else off_tree(W.cost_matrix(w))
     _, st, rels = _check_against_oracle(L.excess.astype(np.float32), L.spare.astype(np.float32), C, w.eps,
                                         w.iters, flags)
     assert np.all(st == 0)
@@ -52,9 +53,11 @@ def test_workloads(cfg, problems, flags, gpu):
 
 
 @pytest.mark.parametrize("seed", range(3))
-def test_mixed_size_classes_in_one_batch(seed, gpu):
+@pytest.mark.parametrize("tree", [True, False])
+def test_mixed_size_classes_in_one_batch(seed, tree, gpu):
     """One batch whose problems fall into different kernel classes: hot-set
-    sizes 1..70 and cold-set sizes 1..250 (register classes and the fallback)."""
+    sizes 1..70 and cold-set sizes 1..250 (register classes and the fallback;
+    all on the tier path with the tree's costs)."""
     rng = np.random.default_rng(50 + seed)
     R, B = 256, 24
     a = np.zeros((B, R), np.float32)
@@ -66,29 +69,32 @@ def test_mixed_size_classes_in_one_batch(seed, gpu):
         a[p, perm[:nh]] = rng.integers(1, 3000, size=nh)
         b[p, perm[nh:nh + nc]] = rng.multinomial(int(a[p].sum()), np.full(nc, 1.0 / nc))
     C = W.cost_matrix_for(R, ("three_tier", 1.0, 3.0, 8.0, 32))
-    _check_against_oracle(a, b, C, 0.08, 300)
+    _check_against_oracle(a, b, C if tree else off_tree(C), 0.08, 300)
 
 
-@pytest.mark.parametrize("flags", [0, taot.SK_NO_REGISTER])
-def test_workload4(flags, gpu):
-    """R = 1024 (about 85 hot and 940 cold ranks): by default the wide
-    register kernel holds the block in one workgroup's registers; with
-    SK_NO_REGISTER it is streamed through device memory."""
+@pytest.mark.parametrize("flags,tree", [(0, True), (0, False), (taot.SK_NO_REGISTER, True)])
+def test_workload4(flags, tree, gpu):
+    """R = 1024 (about 85 hot and 940 cold ranks): by default the tier path
+    for its costs, and for costs that are no tree the wide register kernel,
+    which holds the block in one workgroup's registers; with SK_NO_REGISTER
+    it is streamed through device memory."""
     w = W.WORKLOADS[4]
-    print(f"[sinkhorn parity] workload 4 problem 0 flags {flags}", flush=True)
+    print(f"[sinkhorn parity] workload 4 problem 0 flags {flags} tree {tree}", flush=True)
     _, L = oracle_inputs(w, [0])
-    C = W.cost_matrix(w)
+    C = W.cost_matrix(w) if tree else off_tree(W.cost_matrix(w))
     _, st, rels = _check_against_oracle(L.excess.astype(np.float32), L.spare.astype(np.float32), C, w.eps, w.iters,
                                         flags)
     assert np.all(st == (taot.ST_STREAMED if flags else 0))
 
 
 @pytest.mark.parametrize("R", [300, 1100])
-def test_wide_shapes(R, gpu):
+@pytest.mark.parametrize("tree", [True, False])
+def test_wide_shapes(R, tree, gpu):
     """Problems for the wide register kernel (65..96 hot ranks, or more than
     256 cold ranks), one per columns-per-lane class, with eps small enough to
     trigger the log-domain updates; beside them one problem too large for it
-    (streamed) in the same batch."""
+    (streamed) in the same batch.  With the tree's costs the tier path solves
+    them all and reports the same classes."""
     rng = np.random.default_rng(R)
     if R == 300:
         shapes = [(65, 200), (80, 220), (96, 204), (40, 257), (8, 290)]
@@ -102,8 +108,9 @@ def test_wide_shapes(R, gpu):
         a[p, perm[:nh]] = rng.integers(1, 4000, size=nh)
         b[p, perm[nh:nh + nc]] = rng.multinomial(int(a[p].sum()), np.full(nc, 1.0 / nc)) + 1
     C = W.cost_matrix_for(R, ("three_tier", 1.0, 3.0, 8.0, 32))
+    C = C if tree else off_tree(C)
     for eps, iters in ((0.5, 3), (0.08, 120)):
-        print(f"[sinkhorn parity] wide shapes R={R} eps={eps}", flush=True)
+        print(f"[sinkhorn parity] wide shapes R={R} eps={eps} tree={tree}", flush=True)
         _, st, _ = _check_against_oracle(a, b, C, eps, iters)
         streamed = [nc > 960 for _, nc in shapes]
         assert np.array_equal(st == taot.ST_STREAMED, np.array(streamed)), st
@@ -230,10 +237,11 @@ def test_nonfinite_cost_anywhere(R, where, bad, gpu):
     potentials_check(f[keep], g[keep], ref.f[keep], ref.g[keep], eps, iters)
 
 
-def test_deterministic(gpu):
+@pytest.mark.parametrize("tree", [True, False])
+def test_deterministic(tree, gpu):
     w = W.WORKLOADS[3]
     _, L = oracle_inputs(w, [3, 4])
-    C = W.cost_matrix(w)
+    C = W.cost_matrix(w) if tree else off_tree(W.cost_matrix(w))
     a, b = L.excess.astype(np.float32), L.spare.astype(np.float32)
     T1 = _gpu_sinkhorn(a, b, C, w.eps, w.iters)[0]
     T2 = _gpu_sinkhorn(a, b, C, w.eps, w.iters)[0]
@@ -241,10 +249,12 @@ def test_deterministic(gpu):
 
 
 @pytest.mark.parametrize("nh,nc", [(49, 129), (56, 200), (57, 256), (64, 193), (64, 256)])
-def test_two_wave_rows(nh, nc, gpu):
+@pytest.mark.parametrize("tree", [True, False])
+def test_two_wave_rows(nh, nc, tree, gpu):
     """Hot sets of 49..64 ranks with more than 128 cold ranks: the row block is
-    split over two waves that exchange column sums.  Small eps drives the
-    scalings out of range, so both log-domain absorptions run as well."""
+    split over two waves that exchange column sums (the tier path takes the
+    tree's costs but at the smallest eps).  Small eps drives the scalings out
+    of range, so both log-domain absorptions run as well."""
     rng = np.random.default_rng(nh * 1000 + nc)
     R = nh + nc
     B = 3
@@ -255,8 +265,9 @@ def test_two_wave_rows(nh, nc, gpu):
         a[p, perm[:nh]] = rng.integers(1, 4000, size=nh)
         b[p, perm[nh:]] = rng.multinomial(int(a[p].sum()), np.full(nc, 1.0 / nc)) + 1
     C = W.cost_matrix_for(R, ("three_tier", 1.0, 3.0, 8.0, 32))
+    C = C if tree else off_tree(C)
     for eps, iters in ((0.5, 3), (0.08, 200), (0.02, 120)):
-        print(f"[sinkhorn parity] two-wave nh={nh} nc={nc} eps={eps}", flush=True)
+        print(f"[sinkhorn parity] two-wave nh={nh} nc={nc} eps={eps} tree={tree}", flush=True)
         _check_against_oracle(a, b, C, eps, iters)
 
 
@@ -287,13 +298,14 @@ def test_folded_shapes(gpu):
         _check_against_oracle(a, b, C, eps, iters, taot.SK_WAVES_1)
 
 
-@pytest.mark.parametrize("flags", [0, taot.SK_WAVES_1])
-def test_register_shapes(flags, gpu):
+@pytest.mark.parametrize("flags,tree", [(0, True), (0, False), (taot.SK_WAVES_1, True)])
+def test_register_shapes(flags, tree, gpu):
     """One problem of every register class (1, 2 or 4 columns per lane x 1..8
     chunks of 8 hot ranks) in one batch.  By default a small batch spreads
     each problem over up to four waves (one-chunk problems share a workgroup,
     one wave each); SK_WAVES_1 takes the shapes of large batches (one wave per
-    problem where its rows fit, else two).  Small eps drives the scalings out
+    problem where its rows fit, else two).  With default flags the tier path
+    takes the tree's costs but at the smallest eps.  Small eps drives the scalings out
     of range, so the log-domain updates run too."""
     rng = np.random.default_rng(7 + flags)
     R = 320
@@ -308,6 +320,31 @@ def test_register_shapes(flags, gpu):
         a[p, perm[:nh]] = rng.integers(1, 4000, size=nh)
         b[p, perm[nh:nh + nc]] = rng.multinomial(int(a[p].sum()), np.full(nc, 1.0 / nc)) + 1
     C = W.cost_matrix_for(R, ("three_tier", 1.0, 3.0, 8.0, 32))
+    C = C if tree else off_tree(C)
     for eps, iters in ((0.5, 3), (0.08, 200), (0.02, 120)):
-        print(f"[sinkhorn parity] register shapes flags={flags} eps={eps}", flush=True)
+        print(f"[sinkhorn parity] register shapes flags={flags} tree={tree} eps={eps}", flush=True)
         _check_against_oracle(a, b, C, eps, iters, flags)
+
+
+@pytest.mark.parametrize("B", [1024, 1100])
+def test_large_batch_of_register_problems(B, gpu):
+    """Shared costs that are no tree and default flags, up to and past the
+    batch in which every problem can hold four waves (16 per compute unit):
+    hot sets of 1..70 and cold sets of 1..180 ranks, in one call."""
+    rng = np.random.default_rng(B)
+    R = 256
+    a = np.zeros((B, R), np.float32)
+    b = np.zeros((B, R), np.float32)
+    for p in range(B):
+        nh, nc = int(rng.integers(1, 71)), int(rng.integers(1, 181))
+        perm = rng.permutation(R)
+        a[p, perm[:nh]] = rng.integers(1, 3000, size=nh)
+        b[p, perm[nh:nh + nc]] = rng.multinomial(int(a[p].sum()), np.full(nc, 1.0 / nc))
+    C = off_tree(W.cost_matrix_for(R, ("three_tier", 1.0, 3.0, 8.0, 32)))
+    T, f, g, st = _gpu_sinkhorn(a, b, C, 0.08, 100)
+    assert np.all(st == 0)
+    at = list(range(0, B, 37)) + [B - 1]
+    a64, b64 = a[at].astype(np.float64), b[at].astype(np.float64)
+    ref = O.sinkhorn(a64, b64, C.astype(np.float64), 0.08, 100)
+    sinkhorn_check(T[at], ref.T, a64, b64)
+    potentials_check(f[at], g[at], ref.f, ref.g, 0.08, 100)
