@@ -81,9 +81,9 @@ TRAFFIC = {
     "plan_loads": (os.path.join(ROOT, "profiles", "plan_loads_workload3_traffic.txt"), 3,
                    ["paper_2608_03676_amd/csrc/loads.hip", "paper_2608_03676_amd/csrc/common.h"]),
     "sinkhorn": (os.path.join(ROOT, "profiles", "sinkhorn_workload3_traffic.txt"), 3,
-                 ["paper_2608_03676_amd/csrc/sinkhorn.hip", "paper_2608_03676_amd/csrc/sk_common.h",
-                  "paper_2608_03676_amd/csrc/sk_register.h", "paper_2608_03676_amd/csrc/sk_reg_w2g8.hip",
-                  "paper_2608_03676_amd/csrc/common.h"]),
+                 ["paper_2608_03676_amd/csrc/sinkhorn.hip", "paper_2608_03676_amd/csrc/sk_tier.hip",
+                  "paper_2608_03676_amd/csrc/sk_common.h", "paper_2608_03676_amd/csrc/sk_register.h",
+                  "paper_2608_03676_amd/csrc/sk_reg_w2g8.hip", "paper_2608_03676_amd/csrc/common.h"]),
     "dense": (os.path.join(ROOT, "profiles", "sinkhorn_dense_row_workload4_traffic.txt"), 4,
               ["paper_2608_03676_amd/csrc/sk_dense.hip", "paper_2608_03676_amd/csrc/sk_common.h",
                "paper_2608_03676_amd/csrc/common.h"]),
@@ -151,7 +151,8 @@ def gpu_clocks():
 def measure_peaks(dev):
     """Peak probes P1-P4 (libtaot_probes.so), HIP events on the launch stream,
     best of 5 launches after one warm-up: HBM read GB/s, unpacked fp32 FMA/s,
-    v_exp_f32/s alone and beside as many FMAs, LDS read bytes/s."""
+    v_exp_f32/s alone and beside as many FMAs, LDS read bytes/s; and the HBM
+    write GB/s of torch's fill."""
     import torch
     L = ctypes.CDLL(os.path.join(ROOT, "paper_2608_03676_amd", "libtaot_probes.so"))
     P, I32, SZ = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
@@ -182,7 +183,14 @@ def measure_peaks(dev):
     buf = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     t_hbm = best(lambda: L.taot_probe_hbm_read(ctypes.c_void_p(buf.data_ptr()), nbytes, 16384,
                                                ctypes.c_void_p(out.data_ptr()), sp))
-    del buf
+    words = buf.view(torch.float32)
+
+    def fill():
+        words.fill_(1.0)
+        return 0
+
+    t_fill = best(fill)
+    del buf, words
     it_fma, it_exp, it_lds = 20000, 5000, 20000
     lanes = blocks * 256
     t_fma = best(lambda: L.taot_probe_fma(blocks, it_fma, ctypes.c_void_p(out.data_ptr()), sp))
@@ -193,7 +201,7 @@ def measure_peaks(dev):
     exps = lanes * 64.0 * it_exp / t_exp
     exps_f = lanes * 64.0 * it_exp / t_expf
     return {
-        "hbm_read_GBs": nbytes / t_hbm / 1e9,
+        "hbm_read_GBs": nbytes / t_hbm / 1e9, "hbm_write_GBs": nbytes / t_fill / 1e9,
         "fp32_fma_per_s": fma, "fp32_tflops_unpacked": 2 * fma / 1e12,
         "exp_per_s": exps, "exp_to_fma_rate": exps / fma,
         # exp and FMA issued together take 1.5x the exponentials' time when
@@ -623,7 +631,8 @@ def stage_report(w, K, run, peaks):
     stages["plan_loads"]["traffic"] = traffic
     if peaks:
         stages["plan_loads"]["frac_vs_measured_peak"] = stages["plan_loads"]["achieved"] / peaks["hbm_read_GBs"]
-        stages["sinkhorn"]["frac_vs_measured_peak"] = stages["sinkhorn"]["achieved"] / peaks["hbm_read_GBs"]
+        # (the Sinkhorn's bytes are stores)
+        stages["sinkhorn"]["frac_vs_measured_peak"] = stages["sinkhorn"]["achieved"] / peaks["hbm_write_GBs"]
     for k, f in floor.items():
         stages[k]["floor_ms"] = f
         stages[k]["frac_of_floor"] = f / stages[k]["ms_median"]
