@@ -36,9 +36,20 @@ constexpr int kDnWaves = kDnThreads / kWave;
 constexpr int kDnRowBlock = 64;  // rows per block of the row pass
 constexpr int kDnColBlock = 16;  // columns per block of the column kernel
 constexpr int kDnFixRows = 16;   // rows in flight per thread of an exact column update (32 and 64: slower, fewer waves fit)
-// columns absorbed along with one that has to be (see dense_col_kernel)
-constexpr float kFarLo = 0x1p-16f, kFarHi = 0x1p16f;
 constexpr int kDnDepth = 1;      // row tiles in flight behind the current one
+
+// K~_ij = exp2(F_i + G_j - C'_ij) for C'_ij = cp.  F, G and C' are up to some
+// hundreds and their sum is small, so what F + G rounds away would be an error of
+// that entry alone; it is kept (a two-sum).  A rounding of C' is the same for all
+// entries of a cost.  Error of the plan against 64 bits, 64 problems of R = 1024,
+// 500 iterations: 2.3e-6 without the rest, 8e-8 with it; R = 94, costs of 26, 79 and
+// 105 eps: 6.2e-7 (5.1e-7 when columns were absorbed one at a time) and 2.0e-7.  It costs 1.5 % of that call (30.0 -> 30.5
+// ms).
+__device__ __forceinline__ float kt_entry(float f, float g, float cp) {
+  const float s = f + g, t = s - f;
+  const float rest = (f - (s - t)) + (g - t);
+  return fexp2((s - cp) + rest);
+}
 
 // Row pass, R % 4 == 0 and C 16-byte aligned: the wave-streamed kernel, 16
 // rows per wave, lane l holding the 16-byte groups l + 64 k (k < KQ) of a
@@ -322,7 +333,7 @@ __global__ void __launch_bounds__(kDnThreads) __attribute__((amdgpu_waves_per_eu
         float k[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          k[c] = sa > 0.f && Gc[c] != -INFINITY ? fexp2((fi + Gc[c]) - cur[r][c] * kappa) : 0.f;
+          k[c] = sa > 0.f && Gc[c] != -INFINITY ? kt_entry(fi, Gc[c], cur[r][c] * kappa) : 0.f;
           cs[c] += k[c];
         }
         store_row<VEC, KPT>(S.K + (int64_t)(i0 + r) * R, R, k);
@@ -393,7 +404,7 @@ __global__ void __launch_bounds__(kDnThreads) __attribute__((amdgpu_waves_per_eu
         float k[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          k[c] = Gc[c] != -INFINITY ? fexp2((fi + Gc[c]) - cr[c] * kappa) : 0.f;
+          k[c] = Gc[c] != -INFINITY ? kt_entry(fi, Gc[c], cr[c] * kappa) : 0.f;
           cs[c] += k[c];
         }
         store_row<VEC, KPT>(S.K + (int64_t)i * R, R, k);
@@ -457,7 +468,7 @@ __device__ __forceinline__ float row_exact4(float (&c)[NC], const float (&G)[NC]
   sum = lanes_sum(sum);
   const float fi = flog2(sa) - (mx + flog2(sum));
 #pragma unroll
-  for (int j = 0; j < NC; ++j) c[j] = G[j] != -INFINITY ? fexp2((fi + G[j]) - c[j] * kappa) : 0.f;
+  for (int j = 0; j < NC; ++j) c[j] = G[j] != -INFINITY ? kt_entry(fi, G[j], c[j] * kappa) : 0.f;
   return fi;
 }
 
@@ -592,24 +603,17 @@ dense_roww_kernel(SkParams p, float kappa) {
 // One column half-step for 16 columns of a problem: the 16 thread groups add
 // a sixteenth of the row blocks' partials each (64-byte segments per group)
 // and the first 16 threads set v_j from the group sums (added in group
-// order).  When a v_j leaves [2^-60, 2^60], it and the block's other columns
-// beyond [kFarLo, kFarHi] take the exact log-domain update from C, with their
-// columns of K~ rebuilt.
+// order).  When a v_j leaves [2^-60, 2^60], all the block's columns take the
+// exact log-domain update from C, with their columns of K~ rebuilt.
 //
 // What bounds that update is its traffic: a column of C or K~ alone moves a
 // whole segment per row, the same as the block's 16 columns, whose potentials
 // drift much alike; so the block's other columns are absorbed with the first
 // that has to be, which spares them an update of their own (64 problems of R =
-// 1024, a cost matrix each, 500 iterations: 33.8 -> 30.1 ms).  Columns whose
-// scaling is well inside the range stay: a rebuilt column rounds F_i + G_j - C'_ij
-// per entry, where one that was never absorbed (G_j = 0) shares its rounding with
-// its tier.  R = 94, costs of 26, 79 and 105 eps, against 64 bits: 5.1e-7 with one
-// column at a time, 6.2e-7 with all 16 (30.0 ms), 5.7e-7 with those beyond 2^10,
-// 5.1e-7 beyond 2^16 (30.1 ms), 4.9e-7 beyond 2^40 (30.3 ms).
+// 1024, a cost matrix each, 500 iterations: 33.8 -> 30.5 ms).
 __global__ void __launch_bounds__(kDnThreads, 8) dense_col_kernel(SkParams p, float kappa) {
   constexpr int G = kDnThreads / kDnColBlock;
   __shared__ float ps[G][kDnColBlock], pt[G][kDnColBlock];
-  __shared__ bool far[kDnColBlock];  // the column takes the exact update if one of the block has to
   extern __shared__ __attribute__((aligned(16))) float fixrow[];  // [2][whole tiles of rows]
   const int32_t R = p.R, NB = dense_blocks(R);
   const int32_t chunks = (R + kDnColBlock - 1) / kDnColBlock;
@@ -639,11 +643,9 @@ __global__ void __launch_bounds__(kDnThreads, 8) dense_col_kernel(SkParams p, fl
       const float vn = dj * frcp(xs);
       out = !in_range(vn) && !(p.flags & TAOT_SK_LINEAR);
       S.v[j] = vn;
-      far[cl] = !(vn >= kFarLo && vn <= kFarHi);
     }
   }
   if (__syncthreads_or(out) == 0) return;
-  const bool fix = dj > 0.f && far[cl];
   // F_i and F_i + log2 u_i in LDS; thread group g takes rows g, g + 16, ... with
   // a running maximum and sum over tiles of kDnFixRows rows in flight, and the
   // groups' results meet in group order
@@ -664,7 +666,7 @@ __global__ void __launch_bounds__(kDnThreads, 8) dense_col_kernel(SkParams p, fl
 #pragma unroll
     for (int k = 0; k < kDnFixRows; ++k) c[k] = Cb[at0 + (uint32_t)(min(i0 + k * G, R - 1) * R)];
   };
-  if (fix) {
+  if (dj > 0.f) {
     for (int32_t i0 = grp; i0 < R; i0 += kDnFixRows * G) {
       load_tile(i0);
       // A row without flow has no term, whatever its cost: where c * kappa overflows to -inf,
@@ -685,7 +687,7 @@ __global__ void __launch_bounds__(kDnThreads, 8) dense_col_kernel(SkParams p, fl
   ps[grp][cl] = mx;
   pt[grp][cl] = s;
   __syncthreads();
-  if (!fix) return;
+  if (!(dj > 0.f)) return;
   float M = ps[0][cl];
 #pragma unroll
   for (int g = 1; g < G; ++g) M = fmaxf(M, ps[g][cl]);
@@ -699,7 +701,7 @@ __global__ void __launch_bounds__(kDnThreads, 8) dense_col_kernel(SkParams p, fl
 #pragma unroll
     for (int k = 0; k < kDnFixRows; ++k) {
       const int32_t i = i0 + k * G;
-      if (i < R) S.K[at0 + (uint32_t)(i * R)] = fl[i] != -INFINITY ? fexp2((fl[i] + gc) - c[k] * kappa) : 0.f;
+      if (i < R) S.K[at0 + (uint32_t)(i * R)] = fl[i] != -INFINITY ? kt_entry(fl[i], gc, c[k] * kappa) : 0.f;
     }
   }
   if (grp == 0) {

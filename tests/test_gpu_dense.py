@@ -117,13 +117,13 @@ def test_dense_column_updates_overflowing_costs_without_supply(R, far, gpu):
     _check(a, b, C, 0.02, 40)
 
 
-@pytest.mark.parametrize("R,eps,limit", [(94, 0.038, 5.6e-7), (126, 0.04, 5.1e-7)])
-def test_dense_column_updates_keep_precision(R, eps, limit, gpu):
+@pytest.mark.parametrize("R,eps", [(94, 0.038), (126, 0.04)])
+def test_dense_column_updates_keep_precision(R, eps, gpu):
     """Columns of one block whose scalings differ by tens of binary orders (the
-    ranks of a near and of a far node): absorbing the near ones with the far
-    ones costs accuracy.  Root mean square over the problems of the plan's
-    error against 64 bits; the limit is 1.1 times what one column at a time
-    gives (5.1e-7 and 4.7e-7; all 16 together 6.2e-7 and 5.6e-7)."""
+    ranks of a near and of a far node) are absorbed together.  Root mean square
+    over the problems of the plan's error against 64 bits: rounding F + G per
+    entry gives 4.7e-7 and 5.1e-7 (columns one at a time) to 6.2e-7 (all 16),
+    keeping what it rounds away 2.0e-7 and 2.3e-7."""
     rng = np.random.default_rng(R)
     B = 48
     C = W.cost_matrix_for(R, ("three_tier", 1.0, 3.0, 4.0, 32))
@@ -137,7 +137,7 @@ def test_dense_column_updates_keep_precision(R, eps, limit, gpu):
     T = _dense(a, b, C, eps, 40)[0].astype(np.float64)
     ref = O.sinkhorn(a.astype(float), b.astype(float), C.astype(float), float(np.float32(eps)), 40).T
     err = np.sqrt(((T - ref) ** 2).sum((1, 2)) / (ref ** 2).sum((1, 2)))
-    assert np.sqrt((err ** 2).mean()) <= limit, err
+    assert np.sqrt((err ** 2).mean()) <= 3.5e-7, err
 
 
 def test_dense_stress_shape_per_problem_costs(gpu):
